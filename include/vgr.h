@@ -89,7 +89,8 @@ enum { VGR_KERNEL_GAUSSIAN = 0, VGR_KERNEL_EPANECHNIKOV = 1 };
  *               context's last tuned shape (8x8 until vgr_autotune) [0, 0]
  *   batch       records staged in LDS per rasteriser batch (the block
  *               shape), 32 or 64; 0 = tuned as tile_w/h (64 until
- *               vgr_autotune).  Never changes the result [0]
+ *               vgr_autotune).  Never changes the result.  The colour modes with
+ *               the volumetric opacity stage 64 whatever it says [0]
  *   density     what the `dens` input holds: KAPPA, the density kappa >= 0
  *               itself, or THETA, the paper's density parameter theta, with
  *               kappa = -ln(1 - 0.99 theta) (1/s_x + 1/s_y + 1/s_z) / 3
@@ -181,17 +182,20 @@ typedef struct {
     int64_t pairs_blended;   /*   past the cheap bound test, pairs blended   */
     int64_t visits;          /* wave-level: (Gaussian, pixel slot of a wave)  */
     int64_t visits_full;     /*   steps, and those that took the evaluation   */
-                             /*   branch (some pixel passed the bound test)   */
+                             /*   branch (some pixel passed the bound test);  */
+                             /*   where a wave has a 4x4 block: candidates,   */
+                             /*   and those that reach the block              */
     int64_t bwd_pairs_tested;   /* the same five counts for the backward   */
     int64_t bwd_pairs_full;     /*   rasteriser of the last backward (no    */
                                 /*   pairs tested, and visits = evaluation */
                                 /*   steps, where it reuses the forward's  */
-                                /*   bound-test masks: colour mode, or one */
-                                /*   pixel per lane).  With 8x8 tiles each */
-                                /*   4x4 quarter walks its own Gaussians:  */
-                                /*   bwd_visits counts wave steps (up to   */
-                                /*   four Gaussians each), bwd_visits_full */
-                                /*   (Gaussian, quarter) visits            */
+                                /*   masks: colour mode, or one pixel per  */
+                                /*   lane).  In the colour modes with the  */
+                                /*   volumetric opacity bwd_visits counts  */
+                                /*   wave steps (four (Gaussian, 4x4       */
+                                /*   block) visits each, the last of a     */
+                                /*   batch fewer), bwd_visits_full the     */
+                                /*   visits                                */
     int64_t bwd_pairs_blended;
     int64_t bwd_visits;
     int64_t bwd_visits_full;

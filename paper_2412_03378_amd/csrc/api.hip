@@ -86,6 +86,7 @@ struct vgr_ctx {
     DevBuf tile_key, tile_order, tile_key2, tile_order2;
     DevBuf rgrad, scan_tmp, sort_tmp, words, counters, views, views_b, blk_counts, wg_time;
     DevBuf rs_key, rs_idx, rs_key2, rs_idx2;   // per-tile re-sorting (instance-sized)
+    DevBuf qmask, qclamp, qflag, qused;         // 4x4-block rasterisers (see Buffers)
     DevBuf wseq, wpair, wcount;                // per-pixel window (pair slots, pixels)
     ViewInfo *h_views = nullptr;      // pinned staging: [0] forward, [kMaxViews] backward
     hipEvent_t stage_ev[2] = {};      // recorded after each staging copy
@@ -302,6 +303,10 @@ Buffers make_buffers(vgr_ctx *c)
     b.last_pos = ptr<int32_t>(c->last_pos);
     b.last_id = ptr<int32_t>(c->last_id);
     b.rgrad = ptr<float4>(c->rgrad);
+    b.qmask = ptr<uint64_t>(c->qmask);
+    b.qclamp = ptr<uint64_t>(c->qclamp);
+    b.qflag = ptr<uint32_t>(c->qflag);
+    b.qused = ptr<uint32_t>(c->qused);
     b.wseq = ptr<int2>(c->wseq);
     b.wpair = ptr<float2>(c->wpair);
     b.wcount = ptr<int32_t>(c->wcount);
@@ -311,6 +316,28 @@ Buffers make_buffers(vgr_ctx *c)
     b.wg_time = nullptr;   // set by a forward that times its workgroups
     b.views = ptr<ViewInfo>(c->views);
     return b;
+}
+
+// Buffers in which a forward of `instances` instances leaves what its
+// rasteriser backward reuses: the 4x4 blocks' masks, or the pre-test masks.
+int ensure_kept(vgr_ctx *c, const RenderParams &rp, int64_t instances)
+{
+    int rc;
+    if (raster_quads(rp)) {
+        const size_t nb = (size_t)quad_blocks(rp.tile_w, rp.tile_h);
+        const size_t words = nb * (size_t)quad_batches(instances, rp.total_tiles);
+        if ((rc = ensure(c, c->qflag, sizeof(uint32_t) * words)) ||
+            (rc = ensure(c, c->qmask, 16 * sizeof(uint64_t) * words)) ||
+            (rc = ensure(c, c->qclamp, 16 * sizeof(uint64_t) * words)) ||
+            (rc = ensure(c, c->qused, sizeof(uint32_t) * nb * (size_t)rp.total_tiles)))
+            return rc;
+    } else if (raster_keeps_masks(rp.mode, rp.tile_w, rp.tile_h)) {
+        if ((rc = ensure(c, c->pmask,
+                         8 * (size_t)pmask_words(instances, rp.total_tiles, rp.tile_w, rp.tile_h,
+                                                 rp.batch))))
+            return rc;
+    }
+    return VGR_OK;
 }
 
 int check_ptr(vgr_ctx *c, const void *p, const char *name)
@@ -391,6 +418,7 @@ void vgr_destroy(vgr_ctx *c)
                       &c->words, &c->counters, &c->views, &c->views_b, &c->blk_counts,
                       &c->wg_time,
                       &c->rs_key, &c->rs_idx, &c->rs_key2, &c->rs_idx2,
+                      &c->qmask, &c->qclamp, &c->qflag, &c->qused,
                       &c->wseq, &c->wpair, &c->wcount };
     for (DevBuf *b : all)
         if (b->p) (void)hipFree(b->p);
@@ -582,6 +610,7 @@ int prepare(vgr_ctx *c, const vgr_settings *st, int64_t n, const float *means,
     rp.tile_h = th;
     rp.batch = tb;
     rp.pixel_window = st->pixel_window;
+    rp.ray_moments = raster_quads(rp) ? 1 : 0;
 
     p.vinfo.assign(n_views, ViewInfo{});
     int64_t tiles = 0, pix = 0;
@@ -721,14 +750,16 @@ int enqueue_forward(vgr_ctx *c, const Prepared &p, const float *means, const flo
     mark(c, ST_RANGES);
     // with items, the count gather cleared the ranges and the tile-order counters
     HIP_TRY(c, launch_ranges(b, K, rp.total_tiles, m == 0, s));
-    HIP_TRY(c, launch_tile_order(b, rp.total_tiles, m == 0, s));
+    HIP_TRY(c, launch_tile_order(rp, b, m == 0, s));
     mark_end(c, ST_RANGES);
-    if (cap < 0 && raster_keeps_masks(rp.mode, rp.tile_w, rp.tile_h)) {
-        // (a capture sizes this buffer for its capacity before it starts)
-        if ((rc = ensure(c, c->pmask,
-                         8 * (size_t)pmask_words(K, rp.total_tiles, rp.tile_w, rp.tile_h, rp.batch))))
-            return rc;
+    if (cap < 0) {
+        // (a capture sizes these buffers for its capacity before it starts)
+        if ((rc = ensure_kept(c, rp, K))) return rc;
         b.pmask = ptr<uint64_t>(c->pmask);
+        b.qmask = ptr<uint64_t>(c->qmask);
+        b.qclamp = ptr<uint64_t>(c->qclamp);
+        b.qflag = ptr<uint32_t>(c->qflag);
+        b.qused = ptr<uint32_t>(c->qused);
     }
     if (rp.pixel_window > 0) {
         // (a capture sizes these buffers before it starts)
@@ -745,11 +776,10 @@ int enqueue_forward(vgr_ctx *c, const Prepared &p, const float *means, const flo
     b.wg_time = nullptr;
     c->wg_timed = false;
     if (c->wg_timing && cap < 0) {
-        if ((rc = ensure(c, c->wg_time, 16 * (size_t)(rp.total_tiles > 0 ? rp.total_tiles : 1))))
-            return rc;
+        const int64_t wgs = raster_workgroups(rp);
+        if ((rc = ensure(c, c->wg_time, 16 * (size_t)(wgs > 0 ? wgs : 1)))) return rc;
         b.wg_time = ptr<uint2>(c->wg_time);
-        HIP_TRY(c, launch_fill_u32(reinterpret_cast<uint32_t *>(b.wg_time), 0u,
-                                   4 * (int64_t)rp.total_tiles, s));
+        HIP_TRY(c, launch_fill_u32(reinterpret_cast<uint32_t *>(b.wg_time), 0u, 4 * wgs, s));
         c->wg_timed = true;
     }
     mark(c, ST_RASTER_FWD);
@@ -905,13 +935,13 @@ int vgr_get_stats(vgr_ctx *c, vgr_stats *out)
     out->n_views = c->rp.n_views;
     // load balance of the rasterisers: per compute unit, the summed durations
     // of its workgroups; max over mean
-    const int32_t T = c->rp.total_tiles;
+    const int64_t T = raster_workgroups(c->rp);
     if (c->wg_timed && T > 0 && c->wg_time.bytes >= 16 * (size_t)T) {
         std::vector<uint32_t> wt(4 * (size_t)T);
         HIP_TRY(c, hipMemcpy(wt.data(), c->wg_time.p, 16 * (size_t)T, hipMemcpyDeviceToHost));
         for (int dir = 0; dir < 2; ++dir) {
             std::map<uint32_t, double> busy;
-            for (int32_t k = 0; k < T; ++k) {
+            for (int64_t k = 0; k < T; ++k) {
                 const uint32_t key = wt[2 * ((size_t)dir * T + k)];
                 const uint32_t dur = wt[2 * ((size_t)dir * T + k) + 1];
                 if (dur) busy[key] += dur;
@@ -1029,14 +1059,11 @@ int vgr_graph_capture_calls(vgr_ctx *c, const vgr_settings *st, int64_t n, const
                           cams + off[k], out + off[k], ps[k])))
             return rc;
     const int64_t cap = (int64_t)ceil((double)kmax * capacity_factor) + 4096;
-    int64_t mmax = 0, sort_n = 0, pmw = 0;
+    int64_t mmax = 0, sort_n = 0;
     for (const Prepared &p : ps) {
         mmax = p.m > mmax ? p.m : mmax;
         sort_n = p.sort_n > sort_n ? p.sort_n : sort_n;
-        if (raster_keeps_masks(p.rp.mode, p.rp.tile_w, p.rp.tile_h)) {
-            const int64_t w = pmask_words(cap, p.rp.total_tiles, p.rp.tile_w, p.rp.tile_h, p.rp.batch);
-            pmw = w > pmw ? w : pmw;
-        }
+        if ((rc = ensure_kept(c, p.rp, cap))) return rc;
     }
     if (ps[0].rp.tile_resort &&
         ((rc = ensure(c, c->rs_key, 4 * cap)) || (rc = ensure(c, c->rs_idx, 4 * cap)) ||
@@ -1048,7 +1075,6 @@ int vgr_graph_capture_calls(vgr_ctx *c, const vgr_settings *st, int64_t n, const
         (rc = ensure(c, c->rgrad, sizeof(float4) * 4 * (mmax > 0 ? mmax : 1))) ||
         (rc = ensure(c, c->views_graph, sizeof(ViewInfo) * (size_t)off[n_calls])))
         return rc;
-    if (pmw > 0 && (rc = ensure(c, c->pmask, 8 * (size_t)pmw))) return rc;
     int64_t pixmax = 1;
     for (const Prepared &p : ps) pixmax = p.pix > pixmax ? p.pix : pixmax;
     if (ps[0].rp.pixel_window > 0 &&

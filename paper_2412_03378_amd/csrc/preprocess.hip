@@ -160,6 +160,27 @@ __device__ inline void gauss_view(const ViewInfo &vi, const float *mu, const flo
         g.p[k] = g.L[k * 3] * g.m[0] + g.L[k * 3 + 1] * g.m[1] + g.L[k * 3 + 2] * g.m[2];
 }
 
+// View-space mean and the ray through it in FP64 (their rounding sets how
+// precisely the pixel offsets of small, distant Gaussians are known):
+// u0 = (u0x, u0y, 1) and v0 = L u0.
+struct MeanRay {
+    double mz, u0x, u0y;
+    float v0[3];
+};
+__device__ inline MeanRay mean_ray(const ViewInfo &vi, const float *mu, const GaussView &g)
+{
+    MeanRay r;
+    const double mx = (double)vi.R[0] * mu[0] + (double)vi.R[1] * mu[1] + (double)vi.R[2] * mu[2] + vi.t[0];
+    const double my = (double)vi.R[3] * mu[0] + (double)vi.R[4] * mu[1] + (double)vi.R[5] * mu[2] + vi.t[1];
+    r.mz = (double)vi.R[6] * mu[0] + (double)vi.R[7] * mu[1] + (double)vi.R[8] * mu[2] + vi.t[2];
+    const double rmz = 1.0 / r.mz;
+    r.u0x = mx * rmz;
+    r.u0y = my * rmz;
+    for (int k = 0; k < 3; ++k)
+        r.v0[k] = (float)(g.L[3 * k] * r.u0x + g.L[3 * k + 1] * r.u0y + g.L[3 * k + 2]);
+    return r;
+}
+
 // Screen extent along one image axis (normalised coordinate u = x/z) of the
 // ellipsoid {(x-m)^T S^-1 (x-m) <= 1}: roots of
 // (mz^2 - S22) u^2 - 2 (ma mz - Sa2) u + (ma^2 - Saa) = 0.  The discriminant is
@@ -499,19 +520,11 @@ __global__ __launch_bounds__(256) void preprocess_kernel(RenderParams rp, Buffer
                 rect = make_ushort4((unsigned short)tx0, (unsigned short)ty0, (unsigned short)tx1,
                                     (unsigned short)ty1);
                 key = __float_as_uint(z);
-                // view-space mean and projected centre in FP64: their rounding sets
-                // how precisely the pixel offsets of small, distant Gaussians are known
-                const double mx = (double)vi.R[0] * mu[0] + (double)vi.R[1] * mu[1] + (double)vi.R[2] * mu[2] + vi.t[0];
-                const double my = (double)vi.R[3] * mu[0] + (double)vi.R[4] * mu[1] + (double)vi.R[5] * mu[2] + vi.t[1];
-                const double mzd = (double)vi.R[6] * mu[0] + (double)vi.R[7] * mu[1] + (double)vi.R[8] * mu[2] + vi.t[2];
-                const double rmz = 1.0 / mzd;
-                const double u0x = mx * rmz, u0y = my * rmz;
+                const MeanRay ray = mean_ray(vi, mu, g);
+                const double mzd = ray.mz, u0x = ray.u0x, u0y = ray.u0y;
                 const double cxp = (double)vi.fx * u0x + vi.cx, cyp = (double)vi.fy * u0y + vi.cy;
                 const double hx = rint(cxp), hy = rint(cyp);
-                const float v0[3] = {
-                    (float)(g.L[0] * u0x + g.L[1] * u0y + g.L[2]),
-                    (float)(g.L[3] * u0x + g.L[4] * u0y + g.L[5]),
-                    (float)(g.L[6] * u0x + g.L[7] * u0y + g.L[8]) };
+                const float *v0 = ray.v0;
                 const float mz = (float)mzd;
                 const float ifx = 1.0f / vi.fx, ify = 1.0f / vi.fy;
                 const float A[6] = { g.L[0] * ifx, g.L[1] * ify, g.L[3] * ifx, g.L[4] * ify,
@@ -991,18 +1004,42 @@ __global__ void tile_hist_kernel(const uint2 *__restrict__ ranges, uint32_t *__r
     if (threadIdx.x < 32 && h[threadIdx.x]) atomicAdd(&hist[threadIdx.x], h[threadIdx.x]);
 }
 
+// Shortest list that tile_bucket puts into bucket k < 31.
+__device__ inline uint32_t bucket_min(int k)
+{
+    const int o = 30 - k, lg = o >> 1;
+    return lg == 0 ? 1u : (1u << lg) + ((o & 1) ? 1u << (lg - 1) : 0u);
+}
+
+// d_total[3]: the long tiles, which the colour rasterisers give to one wave per 4x4
+// block: those of the buckets whose lists reach 1 / kLongShare of all instances, at
+// most long_max of them; every tile of a frame that has room for all (long_tiles_max).
+//
+// A region walked by one wave takes about 0.1 us per entry, all regions together
+// about 50 ps per instance, so one list of 1/2000 of the instances takes as long as
+// the whole launch; a wave per block is about four times faster on a list but takes a
+// third more time once the chip is full.  Forward / backward us with 8x8 tiles at
+// 1/4096 and 1/8192 (1/2048 and 1/1024 were slower throughout): 1280x720 with 300k
+// Gaussians 78/120 and 66/105, 600k 118/181 and 133/189, 1.2M 185/273 and 186/289,
+// 2.4M 271/433 and 293/456; 1920x1080 with 1M 253/435 and 256/439.
+constexpr uint32_t kLongShare = 4096;
+
 __global__ void tile_place_kernel(const uint2 *__restrict__ ranges, const uint32_t *__restrict__ hist,
                                   uint32_t *__restrict__ cursor, uint32_t *__restrict__ order,
-                                  int32_t n)
+                                  int32_t n, uint32_t *__restrict__ d_total, uint32_t long_max)
 {
     __shared__ uint32_t base[32], local[32], start[32];
     if (threadIdx.x < 32) local[threadIdx.x] = 0;
     if (threadIdx.x == 0) {
-        uint32_t acc = 0;
+        uint32_t acc = 0, nlong = 0;
+        const uint32_t K = d_total[0];
+        const bool all_long = long_max >= (uint32_t)n;   // a small frame
         for (int k = 0; k < 32; ++k) {
             base[k] = acc;
             acc += hist[k];
+            if (k < 31 && (all_long || bucket_min(k) >= K / kLongShare)) nlong = acc;
         }
+        if (blockIdx.x == 0) d_total[3] = min(nlong, long_max);
     }
     __syncthreads();
     const int32_t t = blockIdx.x * blockDim.x + threadIdx.x;
@@ -1121,6 +1158,34 @@ __device__ inline void splat_view_grad(const GaussView &g, const float *s, const
     gth[2] += (float)(2.0 * H[1] * (D[0] - D[1]));
 }
 
+// The rasteriser's moments in the ray frame (raster_quad.hip: basis ray_frame of
+// v0/|v0|, slot 5 holding sum t - M_22, slots 6-8 Z over sqrt(E) with the signs of
+// its first two taken out) to M, Z and U in the L-frame.
+__device__ inline void ray_to_lframe(const MeanRay &ray, const float *gr, float *Mm, float *Zm,
+                                     float *U)
+{
+    const float x = ray.v0[0], y = ray.v0[1], z = ray.v0[2];
+    const float V2 = __fmaf_rn(x, x, __fmaf_rn(y, y, z * z));
+    const float iV = __builtin_amdgcn_rsqf(V2);
+    const float e = (float)ray.mz * (V2 * iV);   // sqrt(E) = |L m|
+    float B[9];
+    ray_frame(x * iV, y * iV, z * iV, B);
+    const float M[9] = { gr[0], gr[1], gr[2], gr[1], gr[3], gr[4], gr[2], gr[4], gr[9] - gr[5] };
+    const float Z[3] = { -e * gr[6], -e * gr[7], e * gr[8] };
+    const float Ur[3] = { gr[13], gr[14], gr[15] };
+    float MB[9];   // M B
+    for (int i = 0; i < 3; ++i)
+        for (int c = 0; c < 3; ++c)
+            MB[3 * i + c] = fmaf(M[3 * i], B[c], fmaf(M[3 * i + 1], B[3 + c], M[3 * i + 2] * B[6 + c]));
+    int k = 0;
+    for (int a = 0; a < 3; ++a) {
+        for (int c = a; c < 3; ++c)
+            Mm[k++] = fmaf(B[a], MB[c], fmaf(B[3 + a], MB[3 + c], B[6 + a] * MB[6 + c]));
+        Zm[a] = fmaf(B[a], Z[0], fmaf(B[3 + a], Z[1], B[6 + a] * Z[2]));
+        U[a] = fmaf(B[a], Ur[0], fmaf(B[3 + a], Ur[1], B[6 + a] * Ur[2]));
+    }
+}
+
 template <int DEG, bool SPLAT>
 __global__ __launch_bounds__(128) void preprocess_bwd_kernel(
     RenderParams rp, Buffers b, const float *__restrict__ means, const float *__restrict__ quats,
@@ -1189,8 +1254,9 @@ __global__ __launch_bounds__(128) void preprocess_bwd_kernel(
         // near-plane segment: M -= p U^T + U p^T (p = L m) and Z -= U (U = 0 elsewhere)
         float Mm[6] = { gr[0], gr[1], gr[2], gr[3], gr[4], gr[5] };
         float Zm[3] = { gr[6], gr[7], gr[8] };
+        float U[3] = { gr[13], gr[14], gr[15] };
+        if (rp.ray_moments) ray_to_lframe(mean_ray(vi, mu, g), gr, Mm, Zm, U);   // uniform
         if (rp.near_segment) {
-            const float *U = gr + 13;
             Mm[0] -= 2.0f * g.p[0] * U[0];
             Mm[1] -= g.p[0] * U[1] + U[0] * g.p[1];
             Mm[2] -= g.p[0] * U[2] + U[0] * g.p[2];
@@ -1482,8 +1548,9 @@ hipError_t launch_resort_permute(const Buffers &b, const uint32_t *idx, uint32_t
     return hipGetLastError();
 }
 
-hipError_t launch_tile_order(const Buffers &b, int32_t total_tiles, bool clear, hipStream_t s)
+hipError_t launch_tile_order(const RenderParams &rp, const Buffers &b, bool clear, hipStream_t s)
 {
+    const int32_t total_tiles = rp.total_tiles;
     if (total_tiles <= 0) return hipSuccess;
     uint32_t *hist = b.tile_key, *cursor = b.tile_key + 32;   // 64 words of scratch
     if (clear) {
@@ -1492,7 +1559,8 @@ hipError_t launch_tile_order(const Buffers &b, int32_t total_tiles, bool clear, 
     }
     tile_hist_kernel<<<grid_for(total_tiles, 256), 256, 0, s>>>(b.ranges, hist, total_tiles);
     tile_place_kernel<<<grid_for(total_tiles, 256), 256, 0, s>>>(b.ranges, hist, cursor,
-                                                                  b.tile_order, total_tiles);
+                                                                  b.tile_order, total_tiles, b.d_total,
+                                                                  (uint32_t)long_tiles_max(total_tiles, rp.tile_w, rp.tile_h));
     return hipGetLastError();
 }
 

@@ -1,4 +1,6 @@
-// Tile rasteriser, forward and backward, for gfx950 (wave64).
+// Tile rasteriser, forward and backward, for gfx950 (wave64): X-ray mode, the
+// splatting opacity and the per-pixel window.  The colour modes with the volumetric
+// opacity are in raster_quad.hip, which shares the forward walk (raster_walk.h).
 //
 // One wave (64 lanes) owns one screen tile of TW x TH pixels; lane l holds the
 // TW*TH/64 pixels of column l % TW, rows l / TW + k * (64 / TW) ("slot" k).
@@ -14,11 +16,11 @@
 // batch together, reading the three float4 of the bound pre-test first and
 // the other three only when some pixel of the slot passes.  The backward
 // reduces its per-pair gradients per Gaussian, so lanes that share a record
-// walk together: on 8x8 tiles in the volumetric colour modes each 4x4
-// quarter of the tile (16 lanes) walks the records its own pixels' masks
-// name, four records per step; elsewhere the whole wave walks the records
-// that the union of the lanes' masks names, or, where the forward kept no
-// masks, pre-tests each record as the X-ray forward does.
+// walk together: with the per-pixel window (8x8 tiles) each 4x4 quarter of the
+// tile (16 lanes) walks the records its own pixels' masks name, four records
+// per step; elsewhere the whole wave walks the records that the union of the
+// lanes' masks names, or, where the forward kept no masks, pre-tests each
+// record as the X-ray forward does.
 //
 // Per (pixel, Gaussian) pair, with the record (centre h + l, A, v0, mz, K',
 // bound form Q, l; see vgr_internal.h) and d = pixel centre - h - l:
@@ -45,473 +47,17 @@
 // of the lanes on one record are reduced with a transpose-reduce (lane-swap
 // and DPP moves, no LDS), after which each lane holds one total, and added
 // with one atomic instruction (for all four records of a quarter-walk step).
-#include "vgr_internal.h"
+#include "raster_walk.h"
 
 namespace vgr {
 
 namespace {
 
-constexpr int kStageVec = 6;   // record float4 the rasteriser uses (g0..g5)
-
-__device__ __forceinline__ float fast_rsq(float x) { return __builtin_amdgcn_rsqf(x); }
-__device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
-__device__ __forceinline__ float fast_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
-
-// Near-plane segment factor Phi(eta) of a flagged record (K' < 0):
-// eta = (gamma - t_n) / beta = mz (v0 . w) / |w| - zn |w| for the pixel's
-// w = L u, t_n = zn |u| the near-plane crossing of the ray (Sec. 4.2, the
-// integral from t_n on).  qw = |w|^2, rq = 1 / |w|.
-__device__ __forceinline__ float near_eta(float v0x, float v0y, float v0z, float mz, float w0,
-                                          float w1, float w2, float qw, float rq, float zn)
-{
-    const float vw = __fmaf_rn(v0x, w0, __fmaf_rn(v0y, w1, v0z * w2));
-    return __fmaf_rn(mz, vw, -zn * qw) * rq;
-}
-__device__ __forceinline__ float norm_cdf(float e) { return 0.5f * erfcf(-0.70710678f * e); }
-
-// Profile factor of the line integral at D^2 = se num rq2 (with se from the
-// record): exp2(-(log2 e / 2) D^2) for the Gaussian, (1 - D^2)^(3/2) (0 past
-// the support) for the Epanechnikov kernel.
-template <bool EPAN>
-__device__ __forceinline__ float profile(float se, float num, float rq2)
-{
-    if constexpr (EPAN) {
-        const float h2 = fmaxf(1.0f - se * num * rq2, 0.0f);
-        return h2 * __builtin_sqrtf(h2);
-    } else {
-        return fast_exp2(-(se * num * rq2));
-    }
-}
-
-// Timed runs (b.wg_time set) record for each workgroup the constant-rate
-// realtime counter difference between start and end, and a key of the compute unit it ran on (XCC id, then the
-// shader engine, array and CU fields of HW_ID), so that the host can sum the
-// busy time per compute unit (load balance).
-__device__ __forceinline__ uint64_t wg_clock() { return __builtin_amdgcn_s_memrealtime(); }
-__device__ __forceinline__ uint32_t cu_key()
-{
-    const uint32_t hw = __builtin_amdgcn_s_getreg(4 | (31 << 11));    // HW_ID
-    const uint32_t xcc = __builtin_amdgcn_s_getreg(20 | (3 << 11));   // XCC_ID[3:0]
-    return (xcc << 8) | ((hw >> 8) & 0xFFu);
-}
-
-// True if p holds on any active lane: a ballot of the predicate's lane mask,
-// which the branch tests directly.
-__device__ __forceinline__ bool wave_any(bool p) { return __builtin_amdgcn_ballot_w64(p) != 0; }
-
-template <int B>
-struct Stage {
-    float4 g[kStageVec][B];
-    uint32_t item[B];
-};
-
-// Word of the kept pre-test mask of lane `lane` for the batch that starts at
-// list position bs of global tile gt (layout: raster_keeps_masks).
-template <int B>
-__device__ __forceinline__ size_t mask_word(uint32_t bs, int gt, int lane)
-{
-    return (size_t)bs * (64 / B) + 64 * (size_t)gt + lane;
-}
-
-// Fields of the bound pre-test (g0..g2) and of the full evaluation (g3..g5).
-struct PreRec {
-    float hx, hy, lx, ly, Q00, Q01x2, l0x2, l1x2, Q11, A00, A10, A20;
-};
-struct FullRec {
-    float A01, A11, A21, v0x, v0y, v0z, K, se, c0, c1, c2, mz;
-};
-
-template <class ST>
-__device__ __forceinline__ PreRec load_pre(const ST &st, int q)
-{
-    const float4 a = st.g[0][q], b = st.g[1][q], c = st.g[2][q];
-    PreRec r;
-    r.hx = a.x; r.hy = a.y; r.lx = a.z; r.ly = a.w;
-    r.Q00 = b.x; r.Q01x2 = b.y; r.l0x2 = b.z; r.l1x2 = b.w;
-    r.Q11 = c.x; r.A00 = c.y; r.A10 = c.z; r.A20 = c.w;
-    return r;
-}
-
-template <class ST>
-__device__ __forceinline__ FullRec load_full(const ST &st, int q)
-{
-    const float4 a = st.g[3][q], b = st.g[4][q], c = st.g[5][q];
-    FullRec r;
-    r.A01 = a.x; r.A11 = a.y; r.A21 = a.z; r.v0x = a.w;
-    r.v0y = b.x; r.v0z = b.y; r.K = b.z; r.se = b.w;
-    r.c0 = c.x; r.c1 = c.y; r.c2 = c.z; r.mz = c.w;
-    return r;
-}
-
-// One staged record in registers, read at a per-lane index.
-struct RecRegs {
-    float4 g[kStageVec];
-};
-
-template <class ST>
-__device__ __forceinline__ RecRegs load_regs(const ST &st, int q)
-{
-    RecRegs r;
-#pragma unroll
-    for (int v = 0; v < kStageVec; ++v) r.g[v] = st.g[v][q];
-    return r;
-}
-
-__device__ __forceinline__ PreRec pre_of4(const float4 &a, const float4 &b, const float4 &c)
-{
-    PreRec r;
-    r.hx = a.x; r.hy = a.y; r.lx = a.z; r.ly = a.w;
-    r.Q00 = b.x; r.Q01x2 = b.y; r.l0x2 = b.z; r.l1x2 = b.w;
-    r.Q11 = c.x; r.A00 = c.y; r.A10 = c.z; r.A20 = c.w;
-    return r;
-}
-
-__device__ __forceinline__ PreRec pre_of(const RecRegs &x)
-{
-    return pre_of4(x.g[0], x.g[1], x.g[2]);
-}
-
-__device__ __forceinline__ FullRec full_of(const RecRegs &x)
-{
-    FullRec r;
-    r.A01 = x.g[3].x; r.A11 = x.g[3].y; r.A21 = x.g[3].z; r.v0x = x.g[3].w;
-    r.v0y = x.g[4].x; r.v0z = x.g[4].y; r.K = x.g[4].z; r.se = x.g[4].w;
-    r.c0 = x.g[5].x; r.c1 = x.g[5].y; r.c2 = x.g[5].z; r.mz = x.g[5].w;
-    return r;
-}
-
-template <class ST>
-__device__ __forceinline__ void stage_record(ST &st, const Buffers &b, int lane, uint32_t item)
-{
-    const float4 *gp = b.geom + (size_t)item * kRecVec;
-#pragma unroll
-    for (int v = 0; v < kStageVec; ++v) st.g[v][lane] = gp[v];
-    st.item[lane] = item;
-}
-
-// Per-lane terms of the pre-test shared by the lane's pixels (pxc = px + 0.5).
-struct ColTerms {
-    float dx, f0, f1;
-};
-
-__device__ __forceinline__ ColTerms col_terms(const PreRec &r, float pxc)
-{
-    ColTerms c;
-    c.dx = (pxc - r.hx) - r.lx;
-    c.f0 = __fmaf_rn(c.dx, __fmaf_rn(r.Q00, c.dx, r.l0x2), -1.0f);
-    c.f1 = __fmaf_rn(r.Q01x2, c.dx, r.l1x2);
-    return c;
-}
-
-// Bound pre-test of one pixel (pyc = py + 0.5): true if alpha >= alpha_min is
-// possible.  Writes the row offset.
-__device__ __forceinline__ bool pre_test(const PreRec &r, const ColTerms &c, float pyc, float &dy)
-{
-    dy = (pyc - r.hy) - r.ly;
-    const float f = __fmaf_rn(dy, __fmaf_rn(r.Q11, dy, c.f1), c.f0);
-    return !(f > kConicMargin);
-}
-
-struct PairGeom {
-    float a0, a1, a2, w0, w1, w2, n0, n1, n2, num, qw;
-};
-
-__device__ __forceinline__ void pair_geom(const PreRec &p, const FullRec &r, float dx, float dy,
-                                          PairGeom &g)
-{
-    g.a0 = __fmaf_rn(r.A01, dy, p.A00 * dx);
-    g.a1 = __fmaf_rn(r.A11, dy, p.A10 * dx);
-    g.a2 = __fmaf_rn(r.A21, dy, p.A20 * dx);
-    g.w0 = r.v0x + g.a0;
-    g.w1 = r.v0y + g.a1;
-    g.w2 = r.v0z + g.a2;
-    g.n0 = __fmaf_rn(r.v0y, g.a2, -r.v0z * g.a1);
-    g.n1 = __fmaf_rn(r.v0z, g.a0, -r.v0x * g.a2);
-    g.n2 = __fmaf_rn(r.v0x, g.a1, -r.v0y * g.a0);
-    g.num = __fmaf_rn(g.n0, g.n0, __fmaf_rn(g.n1, g.n1, g.n2 * g.n2));
-    g.qw = __fmaf_rn(g.w0, g.w0, __fmaf_rn(g.w1, g.w1, g.w2 * g.w2));
-}
-
-template <int TW, int TH>
-struct TileMap {
-    static constexpr int PPL = TW * TH / 64;
-    static constexpr int RS = 64 / TW;
-    static_assert(TW * TH % 64 == 0 && 64 % TW == 0, "tile shape");
-};
-
-__device__ __forceinline__ int find_view(const ViewInfo *views, int n_views, int gt)
-{
-    int v = 0;
-    for (int k = 1; k < n_views; ++k)
-        if (views[k].tile_off <= gt) v = k;
-    return v;
-}
-
-// Pair counts (per lane) and wave-level visit counts (kept by lane 0): a
-// visit is one Gaussian against one slot of the wave's pixels; a full visit
-// is one that takes the evaluation branch.
-struct Counts {
-    uint32_t test = 0, full = 0, blend = 0, visits = 0, visits_full = 0;
-};
-
 template <int TW, int TH, int MODE, bool COUNT, int B>
 __global__ __launch_bounds__(64) void raster_fwd_kernel(RenderParams rp, Buffers b)
 {
-    static_assert(B == 32 || B == 64, "records per batch");
-    constexpr int PPL = TileMap<TW, TH>::PPL;
-    constexpr int RS = TileMap<TW, TH>::RS;
-    constexpr bool COLOR = MODE != VGR_MODE_XRAY && MODE != kModeXrayNear && MODE != kModeXrayEpan;
-    constexpr bool SPLAT = MODE == kModeSplat;   // colour with the 3DGS splatting alpha
-    constexpr bool NEAR = MODE == kModeColorNear || MODE == kModeXrayNear;
-    constexpr bool EPAN = MODE == kModeColorEpan || MODE == kModeXrayEpan;
     __shared__ Stage<B> st;
-
-    const bool timed = b.wg_time != nullptr;   // uniform
-    const uint64_t t_start = timed ? wg_clock() : 0;
-    const int gt = (int)b.tile_order[blockIdx.x];
-    const int v = find_view(b.views, rp.n_views, gt);
-    const ViewInfo &vi = b.views[v];
-    const int lt = gt - vi.tile_off;
-    const int tx = lt % vi.tiles_x, ty = lt / vi.tiles_x;
-    const int lane = threadIdx.x;
-    const int px = tx * TW + (lane % TW);
-    const int py0 = ty * TH + lane / TW;
-    const int W = vi.width, H = vi.height;
-    const float pxc = (float)px + 0.5f;
-    const float ux = (pxc - vi.cx) / vi.fx;
-
-    float pyc[PPL], un[PPL], T[PPL], C0[PPL], C1[PPL], C2[PPL];
-    int last[PPL];
-    bool act[PPL];
-    Counts n;
-#pragma unroll
-    for (int k = 0; k < PPL; ++k) {
-        const int py = py0 + k * RS;
-        pyc[k] = (float)py + 0.5f;
-        const float uyn = (pyc[k] - vi.cy) / vi.fy;
-        un[k] = sqrtf(ux * ux + uyn * uyn + 1.0f);
-        act[k] = px < W && py < H;
-        T[k] = 1.0f;
-        C0[k] = C1[k] = C2[k] = 0.0f;
-        last[k] = -1;
-    }
-    const uint2 range = b.ranges[gt];
-    const float tau2 = rp.tau2, ymax = rp.ymax, Tmin = rp.T_min;
-    const float amin = rp.amin, amax = rp.amax;
-    const float zn = vi.znear;
-
-    for (uint32_t bs = range.x; bs < range.y; bs += B) {
-        const uint32_t j = bs + lane;
-        if (lane < B && j < range.y) stage_record(st, b, lane, b.inst_val[j]);
-        __syncthreads();
-        const int nb = (int)min((uint32_t)B, range.y - bs);
-        if constexpr (PPL == 1 || COLOR) {
-            // Phase 1: bound pre-test of the whole batch (broadcast records);
-            // bit q of mask[k] marks record q as passing for the lane's slot k.
-            // The two 32-record halves fill 32-bit words, each bit set by one
-            // select of a wave-uniform constant.
-            uint32_t mhalf[2][PPL];
-    #pragma unroll
-            for (int k = 0; k < PPL; ++k) mhalf[1][k] = 0u;   // B = 32: one half
-    #pragma unroll
-            for (int h = 0; h < B / 32; ++h) {
-    #pragma unroll
-                for (int k = 0; k < PPL; ++k) mhalf[h][k] = 0u;
-                const int qend = min(nb, 32 * h + 32);
-                for (int qi = 32 * h; qi < qend; ++qi) {
-                    const float4 g0 = st.g[0][qi], g1 = st.g[1][qi], g2 = st.g[2][qi];
-                    const PreRec pr = pre_of4(g0, g1, g2);
-                    const ColTerms ct = col_terms(pr, pxc);
-                    const uint32_t bit = 1u << (qi & 31);
-    #pragma unroll
-                    for (int k = 0; k < PPL; ++k) {
-                        float dy;
-                        const bool pass = act[k] && pre_test(pr, ct, pyc[k], dy);
-                        mhalf[h][k] |= pass ? bit : 0u;
-                        if (COUNT) {
-                            n.test += act[k] ? 1u : 0u;
-                            const bool anyl = wave_any(act[k]);
-                            n.visits += (lane == 0 && anyl) ? 1u : 0u;
-                        }
-                    }
-                }
-            }
-            uint64_t mask[PPL];
-    #pragma unroll
-            for (int k = 0; k < PPL; ++k) mask[k] = ((uint64_t)mhalf[1][k] << 32) | mhalf[0][k];
-            // kept for the backward (layout: raster_keeps_masks)
-    #pragma unroll
-            for (int k = 0; k < PPL; ++k)
-                b.pmask[mask_word<B>(bs, gt, lane) * PPL + k] = mask[k];
-            // Phase 2: every lane evaluates and blends its own passing records in
-            // list order, one per step (records read from LDS at per-lane
-            // addresses), so a step does useful work on every lane that still has
-            // a record left instead of only on those that pass one shared record.
-    #pragma unroll
-            for (int k = 0; k < PPL; ++k) {
-                uint64_t mk = mask[k];
-                bool has = mk != 0 && act[k];
-                if (wave_any(has)) do {                          // wave-uniform loop
-                    const int qi = has ? (int)__builtin_ctzll(mk) : 0;
-                    mk &= mk - 1;
-                    if (COUNT) {
-                        n.full += has ? 1u : 0u;
-                        n.visits_full += lane == 0 ? 1u : 0u;
-                    }
-                    const RecRegs rr = load_regs(st, qi);
-                    const PreRec pr = pre_of(rr);
-                    const FullRec fr = full_of(rr);
-                    const float dx = (pxc - pr.hx) - pr.lx;
-                    const float dy = (pyc[k] - pr.hy) - pr.ly;
-                    float y, om, wa;   // log2(e) x (volumetric), 1 - alpha, alpha
-                    bool bl;
-                    if constexpr (SPLAT) {
-                        // alpha = o exp(-1/2 d^T C d) (the 3DGS splat)
-                        const float e = __fmaf_rn(dx, __fmaf_rn(fr.A01, dx, fr.A11 * dy),
-                                                  fr.A21 * (dy * dy));
-                        const float al = fr.K * fast_exp2(-e);
-                        bl = has && !(al < amin);
-                        wa = al > amax ? amax : al;
-                        om = 1.0f - wa;
-                        y = 0.0f;
-                    } else {
-                        PairGeom g;
-                        pair_geom(pr, fr, dx, dy, g);
-                        const float rq = fast_rsq(g.qw);
-                        const float ex = profile<EPAN>(fr.se, g.num, rq * rq);
-                        y = (NEAR ? fabsf(fr.K) : fr.K) * un[k] * rq * ex;
-                        if constexpr (NEAR) {
-                            if (fr.K < 0.0f)
-                                y *= norm_cdf(near_eta(fr.v0x, fr.v0y, fr.v0z, fr.mz, g.w0, g.w1,
-                                                       g.w2, g.qw, rq, zn));
-                        }
-                        bl = has && !(y < tau2);
-                        om = fast_exp2(-(y > ymax ? ymax : y));
-                        wa = 1.0f - om;
-                    }
-                    if constexpr (COLOR) {
-                        const float Tn = T[k] * om;
-                        const bool stop = bl && Tn < Tmin;
-                        const bool dob = bl && !stop;
-                        const float wgt = dob ? wa * T[k] : 0.0f;
-                        C0[k] = __fmaf_rn(fr.c0, wgt, C0[k]);
-                        C1[k] = __fmaf_rn(fr.c1, wgt, C1[k]);
-                        C2[k] = __fmaf_rn(fr.c2, wgt, C2[k]);
-                        T[k] = dob ? Tn : T[k];
-                        last[k] = dob ? (int)(bs + qi) : last[k];
-                        act[k] = act[k] && !stop;
-                        if (COUNT) n.blend += dob ? 1u : 0u;
-                    } else {
-                        C0[k] += bl ? y : 0.0f;
-                        last[k] += bl ? 1 : 0;   // number of terms (starts at -1)
-                        if (COUNT) n.blend += bl ? 1u : 0u;
-                    }
-                    has = mk != 0 && act[k];
-                } while (wave_any(has));
-            }
-        } else {
-            // X-ray with several pixels per lane: every record of the list is
-            // summed (no early stop), and one broadcast read per step is
-            // shared by the lane's pixels, which measured faster than a
-            // per-lane walk that re-reads the record for each pixel.
-            for (int qi = 0; qi < nb; ++qi) {
-                if (COLOR) {
-                    bool any = false;
-    #pragma unroll
-                    for (int k = 0; k < PPL; ++k) any |= act[k];
-                    if (!wave_any(any)) break;              // every pixel has stopped
-                }
-                const PreRec pr = load_pre(st, qi);
-                const ColTerms ct = col_terms(pr, pxc);
-    #pragma unroll
-                for (int k = 0; k < PPL; ++k) {
-                    float dy;
-                    const bool near = pre_test(pr, ct, pyc[k], dy);   // always evaluated: sets dy
-                    const bool pass = act[k] && near;
-                    const bool anyp = wave_any(pass);
-                    if (COUNT) {
-                        n.test += act[k] ? 1u : 0u;
-                        const bool anyl = wave_any(act[k]);
-                        n.visits += (lane == 0 && anyl) ? 1u : 0u;
-                        n.visits_full += (lane == 0 && anyp) ? 1u : 0u;
-                    }
-                    if (!anyp) continue;                  // wave-uniform
-                    if (COUNT) n.full += pass ? 1u : 0u;
-                    const FullRec fr = load_full(st, qi);
-                    PairGeom g;
-                    pair_geom(pr, fr, ct.dx, dy, g);
-                    const float rq = fast_rsq(g.qw);
-                    const float ex = profile<EPAN>(fr.se, g.num, rq * rq);
-                    float y = (NEAR ? fabsf(fr.K) : fr.K) * un[k] * rq * ex;
-                    if constexpr (NEAR) {
-                        if (fr.K < 0.0f)
-                            y *= norm_cdf(near_eta(fr.v0x, fr.v0y, fr.v0z, fr.mz, g.w0, g.w1, g.w2,
-                                                   g.qw, rq, zn));
-                    }
-                    const bool bl = pass && !(y < tau2);
-                    if constexpr (COLOR) {
-                        if (!wave_any(bl)) continue;            // wave-uniform
-                        const float om = fast_exp2(-(y > ymax ? ymax : y));
-                        const float Tn = T[k] * om;
-                        const bool stop = bl && Tn < Tmin;
-                        const bool dob = bl && !stop;
-                        const float wgt = dob ? (1.0f - om) * T[k] : 0.0f;
-                        C0[k] = __fmaf_rn(fr.c0, wgt, C0[k]);
-                        C1[k] = __fmaf_rn(fr.c1, wgt, C1[k]);
-                        C2[k] = __fmaf_rn(fr.c2, wgt, C2[k]);
-                        T[k] = dob ? Tn : T[k];
-                        last[k] = dob ? (int)(bs + qi) : last[k];
-                        act[k] = act[k] && !stop;
-                        if (COUNT) n.blend += dob ? 1u : 0u;
-                    } else {
-                        C0[k] += bl ? y : 0.0f;
-                        last[k] += bl ? 1 : 0;   // number of terms (starts at -1)
-                        if (COUNT) n.blend += bl ? 1u : 0u;
-                    }
-                }
-            }
-        }
-        __syncthreads();
-        if (COLOR) {
-            bool any = false;
-#pragma unroll
-            for (int k = 0; k < PPL; ++k) any |= act[k];
-            if (!wave_any(any)) break;                    // every pixel has stopped
-        }
-    }
-
-    const int64_t HW = (int64_t)W * H;
-#pragma unroll
-    for (int k = 0; k < PPL; ++k) {
-        const int py = py0 + k * RS;
-        if (px < W && py < H) {
-            const int64_t idx = (int64_t)py * W + px;
-            const int64_t pidx = vi.pix_off + idx;
-            if (COLOR) {
-                vi.out[idx] = __fmaf_rn(T[k], rp.bg[0], C0[k]);
-                vi.out[HW + idx] = __fmaf_rn(T[k], rp.bg[1], C1[k]);
-                vi.out[2 * HW + idx] = __fmaf_rn(T[k], rp.bg[2], C2[k]);
-                b.T_final[pidx] = T[k];
-                b.last_pos[pidx] = last[k];
-                b.last_id[pidx] = last[k] >= 0
-                    ? (int32_t)((int64_t)b.inst_val[last[k]] - (int64_t)v * rp.n) : -1;
-            } else {
-                vi.out[idx] = C0[k] * kLn2;
-                b.T_final[pidx] = fast_exp2(-C0[k]);
-                b.last_pos[pidx] = (int32_t)range.y - 1;
-                b.last_id[pidx] = last[k] + 1;
-            }
-        }
-    }
-    if (COUNT) {
-        atomicAdd(&b.counters[0], (unsigned long long)n.test);
-        atomicAdd(&b.counters[1], (unsigned long long)n.full);
-        atomicAdd(&b.counters[2], (unsigned long long)n.blend);
-        atomicAdd(&b.counters[3], (unsigned long long)n.visits);
-        atomicAdd(&b.counters[4], (unsigned long long)n.visits_full);
-    }
-    if (timed && lane == 0)
-        b.wg_time[blockIdx.x] = make_uint2(cu_key(), (uint32_t)(wg_clock() - t_start));
+    walk_tile_fwd<TW, TH, MODE, COUNT, B>(rp, b, st, (int)b.tile_order[blockIdx.x], 0, blockIdx.x);
 }
 
 // Sum v[0..15] over the 64 lanes (transpose-reduce).  Afterwards lane l with
@@ -525,66 +71,9 @@ __global__ __launch_bounds__(64) void raster_fwd_kernel(RenderParams rp, Buffers
 //   step 4: lanes l and 7 - l of each 8-lane half row (DPP half mirror) keep
 //           one index each and send the other;
 //   step 5: sums within each quad (DPP quad permutations).
-__device__ __forceinline__ float swap_add32(float &a, float b)
-{
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false,
-                                                    false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
-__device__ __forceinline__ float swap_add16(float a, float b)
-{
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false,
-                                                    false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
-// DPP lane moves (gfx9 encodings): row rotate right by 8, quad permutations
-// [2,3,0,1] and [1,0,3,2].
-constexpr int kDppRowRor8 = 0x128;
-constexpr int kDppQuadXor2 = 0x4E;
-constexpr int kDppQuadXor1 = 0xB1;
-
 constexpr int kDppRowRor4 = 0x124;
 constexpr int kDppRowRor2 = 0x122;
 constexpr int kDppRowRor1 = 0x121;
-
-template <int CTRL>
-__device__ __forceinline__ float dpp_move(float v)
-{
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
-}
-
-template <int CTRL>
-__device__ __forceinline__ uint32_t dpp_move_u(uint32_t v)
-{
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, false);
-}
-
-// With N13 only v[0..12] are summed (v[13..15] are zero): step 1 pairs
-// (v[k], v[k+8]) for k < 5, then (v[5], v[6]) and (v[7], 0), leaving seven
-// slots.  Slot s and the lane bit h that picked the pair member give the
-// index of the total a lane ends with, n13_index(s, h); -1: the lane holds
-// no total.
-__device__ __forceinline__ int n13_index(int s, int h)
-{
-    return s < 5 ? s + 8 * h : (s == 5 ? 5 + h : ((s == 6 && h == 0) ? 7 : -1));
-}
-
-template <bool N13, class SWAP>
-__device__ __forceinline__ void pair_step1(float (&v)[16], SWAP swap_add)
-{
-    if constexpr (N13) {
-#pragma unroll
-        for (int k = 0; k < 5; ++k) v[k] = swap_add(v[k], v[k + 8]);
-        v[5] = swap_add(v[5], v[6]);
-        v[6] = swap_add(v[7], 0.0f);
-        v[7] = 0.0f;
-    } else {
-#pragma unroll
-        for (int k = 0; k < 8; ++k) v[k] = swap_add(v[k], v[k + 8]);
-    }
-}
 
 // Index of the total lane l holds after wave_reduce16 (lanes l & 3 == 0).
 template <bool N13>
@@ -660,44 +149,6 @@ __device__ __forceinline__ void keep_send_add(float (&v)[16], int n, bool hi)
     }
 }
 
-// Step 2 for the pairs (v[k], v[k+4]), k < 3: lanes with bit 3 clear (banks
-// 0-1 of each row) add slot k across l ^ 8, the others slot k + 4, each lane
-// writing the sum of the slot it keeps with one bank-masked DPP add (the
-// compiler forms DPP adds only with every bank enabled, and then needs two
-// selects to route the slots).  The s_nop gives the two wait states a DPP read
-// needs after a VALU write of its source VGPR.
-#define VGR_PAIR_ADD8(D, A, C)                                                   \
-    "v_add_f32_dpp " D ", " A ", " A " row_ror:8 row_mask:0xf bank_mask:0x3\n\t" \
-    "v_add_f32_dpp " D ", " C ", " C " row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
-
-__device__ __forceinline__ void pair_add8x3(float (&v)[16])
-{
-    float r0, r1, r2;
-    asm volatile("s_nop 1\n\t" VGR_PAIR_ADD8("%0", "%3", "%6") VGR_PAIR_ADD8("%1", "%4", "%7")
-                     VGR_PAIR_ADD8("%2", "%5", "%8")
-                 : "=&v"(r0), "=&v"(r1), "=&v"(r2)
-                 : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[4]), "v"(v[5]), "v"(v[6]));
-    v[0] = r0;
-    v[1] = r1;
-    v[2] = r2;
-}
-
-// The same for the four pairs k < 4.
-__device__ __forceinline__ void pair_add8x4(float (&v)[16])
-{
-    float r0, r1, r2, r3;
-    asm volatile("s_nop 1\n\t" VGR_PAIR_ADD8("%0", "%4", "%8") VGR_PAIR_ADD8("%1", "%5", "%9")
-                     VGR_PAIR_ADD8("%2", "%6", "%10") VGR_PAIR_ADD8("%3", "%7", "%11")
-                 : "=&v"(r0), "=&v"(r1), "=&v"(r2), "=&v"(r3)
-                 : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "v"(v[4]), "v"(v[5]),
-                   "v"(v[6]), "v"(v[7]));
-    v[0] = r0;
-    v[1] = r1;
-    v[2] = r2;
-    v[3] = r3;
-}
-#undef VGR_PAIR_ADD8
-
 template <bool N13>
 __device__ __forceinline__ float quarter_reduce16(float (&v)[16], int lane)
 {
@@ -754,12 +205,12 @@ __global__ __launch_bounds__(64) void raster_bwd_kernel(RenderParams rp, Buffers
     constexpr int NCH = COLOR ? 3 : 1;
     // the forward kept its pre-test masks for this shape and mode
     constexpr bool KEEP = COLOR || PPL == 1;
-    // 8x8 tiles: each 4x4 quarter walks the records of its own pixels, so that
-    // one step of the wave handles up to four records (quarter_reduce16).  Colour
-    // modes with the volumetric opacity only: the splatting opacity's and the
-    // X-ray backward's few operations per pair do not pay for the per-lane walk
-    // (measured slower).
-    constexpr bool QUAD = PPL == 1 && COLOR && !SPLAT;
+    // per-pixel window (8x8 tiles): each 4x4 quarter walks the records of its own
+    // pixels, so that one step of the wave handles up to four records
+    // (quarter_reduce16); the splatting opacity's and the X-ray backward's few
+    // operations per pair do not pay for the per-lane walk (measured slower)
+    constexpr bool QUAD = WIN;
+    static_assert(!WIN || (PPL == 1 && COLOR && !SPLAT), "the window's tiles and modes");
     __shared__ Stage<B> st;
 
     const bool timed = b.wg_time != nullptr;   // uniform
@@ -1444,24 +895,11 @@ hipError_t fwd_shape(const RenderParams &rp, const Buffers &b, bool count, hipSt
         if (count) raster_fwd_kernel<TW, TH, kModeSplat, true, B><<<grid, block, 0, s>>>(rp, b);
         else raster_fwd_kernel<TW, TH, kModeSplat, false, B><<<grid, block, 0, s>>>(rp, b);
     } else if (rp.kernel == VGR_KERNEL_EPANECHNIKOV) {
-        if (rp.mode == VGR_MODE_COLOR) {
-            if (count) raster_fwd_kernel<TW, TH, kModeColorEpan, true, B><<<grid, block, 0, s>>>(rp, b);
-            else raster_fwd_kernel<TW, TH, kModeColorEpan, false, B><<<grid, block, 0, s>>>(rp, b);
-        } else {
-            if (count) raster_fwd_kernel<TW, TH, kModeXrayEpan, true, B><<<grid, block, 0, s>>>(rp, b);
-            else raster_fwd_kernel<TW, TH, kModeXrayEpan, false, B><<<grid, block, 0, s>>>(rp, b);
-        }
+        if (count) raster_fwd_kernel<TW, TH, kModeXrayEpan, true, B><<<grid, block, 0, s>>>(rp, b);
+        else raster_fwd_kernel<TW, TH, kModeXrayEpan, false, B><<<grid, block, 0, s>>>(rp, b);
     } else if (rp.near_segment) {
-        if (rp.mode == VGR_MODE_COLOR) {
-            if (count) raster_fwd_kernel<TW, TH, kModeColorNear, true, B><<<grid, block, 0, s>>>(rp, b);
-            else raster_fwd_kernel<TW, TH, kModeColorNear, false, B><<<grid, block, 0, s>>>(rp, b);
-        } else {
-            if (count) raster_fwd_kernel<TW, TH, kModeXrayNear, true, B><<<grid, block, 0, s>>>(rp, b);
-            else raster_fwd_kernel<TW, TH, kModeXrayNear, false, B><<<grid, block, 0, s>>>(rp, b);
-        }
-    } else if (rp.mode == VGR_MODE_COLOR) {
-        if (count) raster_fwd_kernel<TW, TH, VGR_MODE_COLOR, true, B><<<grid, block, 0, s>>>(rp, b);
-        else raster_fwd_kernel<TW, TH, VGR_MODE_COLOR, false, B><<<grid, block, 0, s>>>(rp, b);
+        if (count) raster_fwd_kernel<TW, TH, kModeXrayNear, true, B><<<grid, block, 0, s>>>(rp, b);
+        else raster_fwd_kernel<TW, TH, kModeXrayNear, false, B><<<grid, block, 0, s>>>(rp, b);
     } else {
         if (count) raster_fwd_kernel<TW, TH, VGR_MODE_XRAY, true, B><<<grid, block, 0, s>>>(rp, b);
         else raster_fwd_kernel<TW, TH, VGR_MODE_XRAY, false, B><<<grid, block, 0, s>>>(rp, b);
@@ -1477,24 +915,11 @@ hipError_t bwd_shape(const RenderParams &rp, const Buffers &b, bool count, hipSt
         if (count) raster_bwd_kernel<TW, TH, kModeSplat, true, B><<<grid, block, 0, s>>>(rp, b);
         else raster_bwd_kernel<TW, TH, kModeSplat, false, B><<<grid, block, 0, s>>>(rp, b);
     } else if (rp.kernel == VGR_KERNEL_EPANECHNIKOV) {
-        if (rp.mode == VGR_MODE_COLOR) {
-            if (count) raster_bwd_kernel<TW, TH, kModeColorEpan, true, B><<<grid, block, 0, s>>>(rp, b);
-            else raster_bwd_kernel<TW, TH, kModeColorEpan, false, B><<<grid, block, 0, s>>>(rp, b);
-        } else {
-            if (count) raster_bwd_kernel<TW, TH, kModeXrayEpan, true, B><<<grid, block, 0, s>>>(rp, b);
-            else raster_bwd_kernel<TW, TH, kModeXrayEpan, false, B><<<grid, block, 0, s>>>(rp, b);
-        }
+        if (count) raster_bwd_kernel<TW, TH, kModeXrayEpan, true, B><<<grid, block, 0, s>>>(rp, b);
+        else raster_bwd_kernel<TW, TH, kModeXrayEpan, false, B><<<grid, block, 0, s>>>(rp, b);
     } else if (rp.near_segment) {
-        if (rp.mode == VGR_MODE_COLOR) {
-            if (count) raster_bwd_kernel<TW, TH, kModeColorNear, true, B><<<grid, block, 0, s>>>(rp, b);
-            else raster_bwd_kernel<TW, TH, kModeColorNear, false, B><<<grid, block, 0, s>>>(rp, b);
-        } else {
-            if (count) raster_bwd_kernel<TW, TH, kModeXrayNear, true, B><<<grid, block, 0, s>>>(rp, b);
-            else raster_bwd_kernel<TW, TH, kModeXrayNear, false, B><<<grid, block, 0, s>>>(rp, b);
-        }
-    } else if (rp.mode == VGR_MODE_COLOR) {
-        if (count) raster_bwd_kernel<TW, TH, VGR_MODE_COLOR, true, B><<<grid, block, 0, s>>>(rp, b);
-        else raster_bwd_kernel<TW, TH, VGR_MODE_COLOR, false, B><<<grid, block, 0, s>>>(rp, b);
+        if (count) raster_bwd_kernel<TW, TH, kModeXrayNear, true, B><<<grid, block, 0, s>>>(rp, b);
+        else raster_bwd_kernel<TW, TH, kModeXrayNear, false, B><<<grid, block, 0, s>>>(rp, b);
     } else {
         if (count) raster_bwd_kernel<TW, TH, VGR_MODE_XRAY, true, B><<<grid, block, 0, s>>>(rp, b);
         else raster_bwd_kernel<TW, TH, VGR_MODE_XRAY, false, B><<<grid, block, 0, s>>>(rp, b);
@@ -1526,10 +951,16 @@ hipError_t bwd_batch(const RenderParams &rp, const Buffers &b, bool count, hipSt
 
 }  // namespace
 
+int64_t raster_workgroups(const RenderParams &rp)
+{
+    return raster_quads(rp) ? color_workgroups(rp) : rp.total_tiles;
+}
+
 hipError_t launch_raster_fwd(const RenderParams &rp, const Buffers &b, bool count, hipStream_t s)
 {
     if (rp.total_tiles <= 0) return hipSuccess;
     if (rp.pixel_window > 0) return window_fwd(rp, b, s);
+    if (raster_quads(rp)) return launch_color_fwd(rp, b, count, s);
     return rp.batch == 32 ? fwd_batch<32>(rp, b, count, s) : fwd_batch<64>(rp, b, count, s);
 }
 
@@ -1537,6 +968,7 @@ hipError_t launch_raster_bwd(const RenderParams &rp, const Buffers &b, bool coun
 {
     if (rp.total_tiles <= 0) return hipSuccess;
     if (rp.pixel_window > 0) return window_bwd(rp, b, s);
+    if (raster_quads(rp)) return launch_color_bwd(rp, b, count, s);
     return rp.batch == 32 ? bwd_batch<32>(rp, b, count, s) : bwd_batch<64>(rp, b, count, s);
 }
 

@@ -83,6 +83,8 @@ constexpr int kModeColorEpan = 5, kModeXrayEpan = 6;
 // - zn |w| (w' = w/|w|) and h = phi(eta)/Phi(eta), the w' w'^T weight in M
 // becomes t (1 + h (eta + 2 zn |w|)), and the preprocess backward subtracts
 // (Lm) U^T + U (Lm)^T from M and adds L^T U to dL/dm.
+// With ray_moments the rotation-dependent slots are in the ray frame (ray_frame;
+// raster_quad.hip says which products), and the preprocess backward turns them back.
 
 struct ViewInfo {
     float R[9];
@@ -119,6 +121,7 @@ struct RenderParams {
     int32_t tile_resort; // per-tile order by the depth of the maximum on the tile-centre ray
     int32_t kernel;      // VGR_KERNEL_GAUSSIAN or VGR_KERNEL_EPANECHNIKOV
     int32_t batch;       // records staged per rasteriser batch: 32 or 64
+    int32_t ray_moments; // the rasteriser backward's moments are in the ray frame
     int32_t pixel_window;// per-pixel re-sorting window W (0: off; 8x8 tiles, batch 64)
 };
 
@@ -152,6 +155,14 @@ struct Buffers {
                          // batch of a tile list, written by the forward where
                          // raster_keeps_masks() and read by the backward (with
                          // the per-pixel window: the pairs composited)
+    // colour with the volumetric opacity (raster_quads()): what the backward needs
+    // of the forward's decisions, per 4x4 pixel block q of a tile (region by region,
+    // four blocks per 8x8 region) and batch of 64 list entries, bq = quad_batch() *
+    // blocks + q:
+    uint64_t *qmask;     // at 16 bq + p: entries that pixel p of the block blended
+    uint64_t *qclamp;    // the same for clamped entries (valid where qflag says so)
+    uint32_t *qflag;     // at bq: kFlagClamp, kFlagOdd
+    uint32_t *qused;     // at tile * blocks + q: batches up to the last that blended
     // per-pixel window (pixel_window > 0), capacity * 64 slots each:
     int2 *wseq;          // the k-th composited pair of tile lane l (tile list
                          // starting at s) at window_seq(s, k, l) = (s + k) 64 + l:
@@ -164,13 +175,13 @@ struct Buffers {
     uint32_t *blk_counts;// preprocess blocks: instances per block
     uint32_t *d_total;   // [0] = instance count K, [1] overflow flag, [4] K from the
                          // preprocess, [6] items with instances (the first of the
-                         // depth order)
+                         // depth order), [3] long tiles (the first of tile_order)
     uint32_t *h_total;   // or null: pinned host words (device address) that the totals
                          // kernel fills with d_total[4] at [0] and d_total[6] at [2]
     unsigned long long *counters;  // pair and visit counters: forward [0..4], backward [8..12]
-    uint2 *wg_time;      // timed runs (else null): per rasteriser workgroup (launch slot) the
-                         // compute unit key and its duration in clock ticks, forward
-                         // at [0, total tiles), backward at [total tiles, 2 total tiles)
+    uint2 *wg_time;      // timed runs (else null): per rasteriser workgroup the compute
+                         // unit key and its duration in clock ticks, forward at
+                         // [0, G), backward at [G, 2 G) for G = raster_workgroups()
     const ViewInfo *views;
 };
 
@@ -189,6 +200,55 @@ inline int64_t pmask_words(int64_t instances, int32_t total_tiles, int tile_w, i
                            int batch)
 {
     return (instances * (64 / batch) + 64 * (int64_t)total_tiles) * (int64_t)(tile_w * tile_h / 64);
+}
+
+// Calls of the colour rasterisers in raster_quad.hip (volumetric opacity, no per-pixel
+// window).
+inline bool raster_quads(const RenderParams &rp)
+{
+    return rp.mode == VGR_MODE_COLOR && rp.alpha_model == VGR_ALPHA_VOLUMETRIC &&
+           rp.pixel_window == 0;
+}
+__host__ __device__ inline int quad_blocks(int tile_w, int tile_h)
+{
+    return tile_w * tile_h / 16;
+}
+// First batch of tile t whose list starts at `start`: a tile of len entries has
+// at most len / 64 + 1 batches, so the tiles' batches do not overlap.
+__host__ __device__ inline size_t quad_batch(uint32_t start, int t)
+{
+    return (size_t)(start >> 6) + (size_t)t;
+}
+// qflag: some pair of the batch was clamped (qclamp is valid); some colour of the
+// batch is not finite.
+constexpr uint32_t kFlagClamp = 1u, kFlagOdd = 2u;
+// Most tiles the colour rasterisers treat as long (one wave per 4x4 block, the first
+// d_total[3] of tile_order): 2048 regions of 8x8 pixels, whose 8192 waves fill the
+// chip once, or every tile of a frame of at most 8192 regions (640x480 with 8x8 tiles:
+// 93 / 92 us as blocks, 271 / 263 as regions; 1280x720 with 600k Gaussians, 14400
+// regions: slower as blocks).
+inline __host__ __device__ int32_t long_tiles_max(int32_t total_tiles, int tile_w, int tile_h)
+{
+    const int32_t regions = tile_w * tile_h / 64;
+    const int32_t cap = (int64_t)total_tiles * regions <= 8192 ? total_tiles : 2048 / regions;
+    return cap < total_tiles ? cap : total_tiles;
+}
+inline int64_t quad_batches(int64_t instances, int32_t total_tiles)
+{
+    return instances / 64 + total_tiles + 1;
+}
+
+// Orthonormal basis (rows e0, e1, e2 = v) of the unit vector v, the frame of the
+// rasteriser backward's moments: Duff et al., "Building an Orthonormal Basis,
+// Revisited", JCGT 6(1), 2017.  The branch on the sign of v.z makes it
+// discontinuous there, so every user passes the same bits of v.z.
+__device__ inline void ray_frame(float x, float y, float z, float (&B)[9])
+{
+    const float s = __builtin_copysignf(1.0f, z);
+    const float a = -__builtin_amdgcn_rcpf(s + z), c = x * y * a;
+    B[0] = __fmaf_rn(s * x * x, a, 1.0f); B[1] = s * c; B[2] = -s * x;
+    B[3] = c; B[4] = __fmaf_rn(y * y, a, s); B[5] = -y;
+    B[6] = x; B[7] = y; B[8] = z;
 }
 
 // ---- launches (each returns hipSuccess or the first error) ----
@@ -226,11 +286,16 @@ hipError_t launch_resort_permute(const Buffers &b, const uint32_t *idx, uint32_t
                                  uint32_t *tmp_val, int64_t bound, hipStream_t s);
 // Order tiles by decreasing list length (heaviest first) into b.tile_order.
 // clear: zero its counters first (done by launch_gather_counts when it ran).
-hipError_t launch_tile_order(const Buffers &b, int32_t total_tiles, bool clear, hipStream_t s);
+hipError_t launch_tile_order(const RenderParams &rp, const Buffers &b, bool clear, hipStream_t s);
 hipError_t launch_raster_fwd(const RenderParams &rp, const Buffers &b, bool count,
                              hipStream_t s);
 hipError_t launch_raster_bwd(const RenderParams &rp, const Buffers &b, bool count,
                              hipStream_t s);
+int64_t raster_workgroups(const RenderParams &rp);
+// Forward and backward of colour with the volumetric opacity, and their workgroups.
+int64_t color_workgroups(const RenderParams &rp);
+hipError_t launch_color_fwd(const RenderParams &rp, const Buffers &b, bool count, hipStream_t s);
+hipError_t launch_color_bwd(const RenderParams &rp, const Buffers &b, bool count, hipStream_t s);
 // Per-pixel window: bytes of the pair buffers per instance of capacity.
 constexpr int64_t kWindowBytesPerInstance = 64 * (8 + 8);
 // Entry k of tile lane `lane`'s compositing sequence (tile list starting at
