@@ -92,9 +92,11 @@ __device__ __forceinline__ FullRec full_of(const RecRegs &x)
     return r;
 }
 
-// Stage one record; returns its g5 (the colour).
+// Stage one record; returns its g5 (the colour).  wild: a field of the pre-test is not
+// finite.
 template <class ST>
-__device__ __forceinline__ float4 stage_record(ST &st, const Buffers &b, int lane, uint32_t item)
+__device__ __forceinline__ float4 stage_record(ST &st, const Buffers &b, int lane, uint32_t item,
+                                               bool &wild)
 {
     const float4 *gp = b.geom + (size_t)item * kRecVec;
     RecRegs r;
@@ -103,7 +105,18 @@ __device__ __forceinline__ float4 stage_record(ST &st, const Buffers &b, int lan
 #pragma unroll
     for (int v = 0; v < kStageVec; ++v) st.g[v][lane] = r.g[v];
     st.item[lane] = item;
+    float sum = fabsf(r.g[2].x);
+    sum += fabsf(r.g[0].x) + fabsf(r.g[0].y) + fabsf(r.g[0].z) + fabsf(r.g[0].w);
+    sum += fabsf(r.g[1].x) + fabsf(r.g[1].y) + fabsf(r.g[1].z) + fabsf(r.g[1].w);
+    wild = !(sum < INFINITY);
     return r.g[5];
+}
+
+template <class ST>
+__device__ __forceinline__ float4 stage_record(ST &st, const Buffers &b, int lane, uint32_t item)
+{
+    bool wild;
+    return stage_record(st, b, lane, item, wild);
 }
 
 // Per-lane terms of the pre-test shared by the lane's pixels (pxc = px + 0.5).
@@ -129,19 +142,15 @@ __device__ __forceinline__ bool pre_test(const PreRec &r, const ColTerms &c, flo
     return !(f > kConicMargin);
 }
 
-// m shifted left by one, with the pre-test's result as bit 0 (the compare leaves it in
-// VCC, which the add takes as carry: two instructions where a select and an OR
-// take three).
-__device__ __forceinline__ void shift_in_pass(const PreRec &r, const ColTerms &c, float pyc,
-                                              uint32_t &m)
+// Margin left by the pre-test at one pixel (pyc = py + 0.5): negative where alpha <
+// alpha_min for sure.  A NaN made here is positive; the negated factors are finite
+// (records with fields that are not skip the pre-test).
+__device__ __forceinline__ float pre_margin(const PreRec &r, float pxc, float pyc)
 {
-    const float dy = (pyc - r.hy) - r.ly;
-    const float f = __fmaf_rn(dy, __fmaf_rn(r.Q11, dy, c.f1), c.f0);
-    asm("v_cmp_nlt_f32 vcc, %1, %2\n\t"
-        "v_addc_co_u32 %0, vcc, %0, %0, vcc"
-        : "+v"(m)
-        : "s"(kConicMargin), "v"(f)
-        : "vcc");
+    const float dx = (pxc - r.hx) - r.lx, dy = (pyc - r.hy) - r.ly;
+    const float g0 = __fmaf_rn(-dx, __fmaf_rn(r.Q00, dx, r.l0x2), 1.0f + kConicMargin);
+    const float f1 = __fmaf_rn(r.Q01x2, dx, r.l1x2);
+    return __fmaf_rn(-dy, __fmaf_rn(r.Q11, dy, f1), g0);
 }
 
 // Index of the lowest bit of m (31 for m = 0).
@@ -255,6 +264,7 @@ __device__ __forceinline__ void walk_tile_fwd(const RenderParams &rp, const Buff
     for (uint32_t bs = range.x; bs < range.y; bs += B) {
         const uint32_t j = bs + lane;
         bool odd = false;   // a colour that is not finite
+        bool wild = false;  // a pre-test field that is not
         int nb = (int)min((uint32_t)B, range.y - bs);
         bool keep = lane < B && j < range.y;
         int at = lane;      // where the lane's record goes
@@ -266,17 +276,21 @@ __device__ __forceinline__ void walk_tile_fwd(const RenderParams &rp, const Buff
             at = __builtin_popcountll(km & ((1ull << lane) - 1ull));
         }
         if (keep) {
-            const float4 c = stage_record(st, b, at, item);
+            const float4 c = stage_record(st, b, at, item, wild);
             odd = BLOCKS && !(fabsf(c.x) + fabsf(c.y) + fabsf(c.z) < INFINITY);
             if constexpr (CULL) st.item[at] = (uint32_t)lane;   // its entry in the batch
         }
         if (lane < B && j + B < range.y) item = b.inst_val[j + B];
+        const bool bad = wave_any(wild);   // the batch's records pass the pre-test untested
         __syncthreads();
         if constexpr (PPL == 1 || COLOR) {
             // Phase 1: bound pre-test of the whole batch (broadcast records);
             // bit q of mask[k] marks record q as passing for the lane's slot k.
-            // The two 32-record halves fill 32-bit words, which shift one bit a record
-            // (so the bits come in reverse).
+            // The two 32-record halves fill 32-bit words with the sign bits of the
+            // margins, one shift a record (so they come in reverse): one instruction
+            // after the margin, where a compare and an add of its lane mask take two
+            // and two wait states between them (476 -> 450 us at 3M Gaussians,
+            // 1600x1064).
             uint32_t mhalf[2][PPL];
     #pragma unroll
             for (int k = 0; k < PPL; ++k) mhalf[1][k] = 0u;   // B = 32: one half
@@ -287,10 +301,10 @@ __device__ __forceinline__ void walk_tile_fwd(const RenderParams &rp, const Buff
                 const int qend = min(nb, 32 * h + 32);
                 for (int qi = 32 * h; qi < qend; ++qi) {
                     const PreRec pr = pre_of4(st.g[0][qi], st.g[1][qi], st.g[2][qi]);
-                    const ColTerms ct = col_terms(pr, pxc);
     #pragma unroll
                     for (int k = 0; k < PPL; ++k) {
-                        shift_in_pass(pr, ct, pyc[k], mhalf[h][k]);
+                        mhalf[h][k] = __builtin_amdgcn_alignbit(
+                            mhalf[h][k], __float_as_uint(pre_margin(pr, pxc, pyc[k])), 31);
                         if (COUNT) {
                             n.test += __builtin_amdgcn_inverse_ballot_w64(alive[k]) ? 1u : 0u;
                             n.visits += (lane == 0 && alive[k] != 0) ? 1u : 0u;
@@ -300,7 +314,8 @@ __device__ __forceinline__ void walk_tile_fwd(const RenderParams &rp, const Buff
                 const int m = qend - 32 * h;   // uniform
     #pragma unroll
                 for (int k = 0; k < PPL; ++k)
-                    mhalf[h][k] = m > 0 ? __builtin_bitreverse32(mhalf[h][k]) >> (32 - m) : 0u;
+                    mhalf[h][k] = m > 0 ? (bad ? ~0u : ~__builtin_bitreverse32(mhalf[h][k])) >> (32 - m)
+                                        : 0u;
             }
             uint64_t mask[PPL];
     #pragma unroll
