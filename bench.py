@@ -34,16 +34,15 @@ if ROOT not in sys.path:
 #     n = v0 x a, |n|^2, |w|^2 (37), rsq (1), exponent and exp2 (4),
 #     K' |u| r exp2 (3), skip compare (1)                              46
 #   forward compositing of blended pairs (clamp, exp2, T(1-a), stop test,
-#     alpha, weight, colour FMAs)                                      12   (X-ray sum: 1)
-#   backward of blended pairs: compositing replay (clamp, exp2, rcp, T,
-#     g.c, dL/dalpha, colour gradient, g.(colour behind) update) 25 (X-ray:
-#     1), moment accumulation (t, sum t, z = mz (w x n)/|w|^2, w/|w|, Z, M) 54
-#   a backward that reuses the forward's pre-test masks (colour mode, or one
-#     pixel per lane) tests nothing and recomputes d_x, d_y (4) per pair past
-#     the pre-test                                                      4
-F_TEST, F_SHARED, F_FULL, F_OFFSETS = 7, 8, 46, 4
-F_BLEND_FWD = {"color": 12, "xray": 1}
-F_BLEND_BWD = {"color": 25 + 54, "xray": 1 + 54}
+#     alpha, weight, colour FMAs)                                      12
+#   backward of blended pairs, in the ray frame (offsets and integral 36,
+#     replay 25, moments 23)                                           84
+#   X-ray, per pair of a reached 8x8 region: integral 19 (a0, w2, |w|^2, rsq,
+#     exponent, exp2, y, cut), forward sum 1, backward t, T, 1 - D^2 and the
+#     row sums 22
+F_TEST, F_SHARED, F_FULL = 7, 8, 46
+F_BLEND_FWD, F_BLEND_BWD = 12, 84
+F_XRAY_FULL, F_XRAY_FWD, F_XRAY_BWD = 19, 1, 22
 PEAK_FP32 = 157.3e12    # MI355X published FP32 vector peak (FLOP/s)
 CALIB_COPY_BYTES = 1 << 28   # plain device copy used to calibrate the HBM byte counters
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_raster_8x8_1M_1080p.json")
@@ -51,8 +50,10 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_raster_8x8_1M_1080p.json"
 
 def _kernel_source_hash():
     import hashlib
-    src = os.path.join(ROOT, "paper_2412_03378_amd", "csrc", "raster.hip")
-    return hashlib.sha256(open(src, "rb").read()).hexdigest()[:16]
+    h = hashlib.sha256()
+    for name in ("raster_quad.hip", "raster_walk.h", "raster_common.h"):
+        h.update(open(os.path.join(ROOT, "paper_2412_03378_amd", "csrc", name), "rb").read())
+    return h.hexdigest()[:16]
 
 
 def _traffic(kernel):
@@ -70,9 +71,11 @@ def _traffic(kernel):
 
 
 def _flops(tested, full, blended, ppl, mode, direction):
-    fb = F_BLEND_FWD[mode] if direction == "fwd" else F_BLEND_BWD[mode]
-    offs = F_OFFSETS if direction == "bwd" and (mode == "color" or ppl == 1) else 0
-    return tested * (F_TEST + F_SHARED / ppl) + full * (F_FULL + offs) + blended * fb
+    if mode == "xray":   # culled per region, no pre-test of pairs
+        return full * F_XRAY_FULL + blended * (F_XRAY_FWD if direction == "fwd" else F_XRAY_BWD)
+    if direction == "bwd":
+        return blended * F_BLEND_BWD
+    return tested * (F_TEST + F_SHARED / ppl) + full * F_FULL + blended * F_BLEND_FWD
 
 
 def _raster_rates(r, call, ppl, mode):
@@ -654,9 +657,9 @@ def write_traffic(fetch_csv, write_csv, out_path=TRAFFIC_FILE):
         scale = CALIB_COPY_BYTES / ref
         res[counter + "_scale"] = scale
         for k, vs in per.items():
-            for short in ("raster_fwd_kernel", "raster_bwd_kernel"):
+            for short in ("color_fwd_kernel", "color_bwd_kernel"):
                 if short in k and "true>" not in k:       # timed (non-counting) variants
-                    key = short.replace("_kernel", "")
+                    key = short.replace("color", "raster").replace("_kernel", "")
                     d = res["kernels"].setdefault(key, {})
                     d[counter + "_KiB_median"] = statistics.median(vs)
                     d[counter.lower() + "_bytes"] = statistics.median(vs) * 1024.0 * scale

@@ -331,7 +331,7 @@ int ensure_kept(vgr_ctx *c, const RenderParams &rp, int64_t instances)
             (rc = ensure(c, c->qclamp, 16 * sizeof(uint64_t) * words)) ||
             (rc = ensure(c, c->qused, sizeof(uint32_t) * nb * (size_t)rp.total_tiles)))
             return rc;
-    } else if (raster_keeps_masks(rp.mode, rp.tile_w, rp.tile_h)) {
+    } else if (!raster_xray(rp)) {
         if ((rc = ensure(c, c->pmask,
                          8 * (size_t)pmask_words(instances, rp.total_tiles, rp.tile_w, rp.tile_h,
                                                  rp.batch))))
@@ -610,7 +610,7 @@ int prepare(vgr_ctx *c, const vgr_settings *st, int64_t n, const float *means,
     rp.tile_h = th;
     rp.batch = tb;
     rp.pixel_window = st->pixel_window;
-    rp.ray_moments = raster_quads(rp) ? 1 : 0;
+    rp.ray_moments = raster_quads(rp) || raster_xray(rp) ? 1 : 0;
 
     p.vinfo.assign(n_views, ViewInfo{});
     int64_t tiles = 0, pix = 0;

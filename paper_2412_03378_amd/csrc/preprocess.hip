@@ -181,6 +181,42 @@ __device__ inline MeanRay mean_ray(const ViewInfo &vi, const float *mu, const Ga
     return r;
 }
 
+// 1/sqrt(x): v_rsq_f64 (at least single precision) and a Newton step.
+__device__ inline double rsqrt_f64(double x)
+{
+    const double y = __builtin_amdgcn_rsq(x);
+    return y * (1.5 - 0.5 * x * y * y);
+}
+
+// X-ray mode's ray frame: ray_frame's basis over |v0|, turned about e2 by the angle with
+// cosine and sine cs so that e1 . A's first column is zero.  r: r00, r01, r11 and the
+// e2 row s0, s1 (A's columns are w per pixel offset in x and y); rV = 1/|v0|.
+__device__ inline void ray_axes(const float *v0, const float (&A)[6], double (&r)[5], double (&cs)[2],
+                                double &rV)
+{
+    const float x = v0[0], y = v0[1], z = v0[2];
+    const float V2 = __fmaf_rn(x, x, __fmaf_rn(y, y, z * z));
+    const float iV = __builtin_amdgcn_rsqf(V2);
+    float B[9];
+    ray_frame(x * iV, y * iV, z * iV, B);
+    const double V2d = (double)x * x + (double)y * y + (double)z * z;
+    rV = rsqrt_f64(V2d);
+    double q[6];
+    for (int i = 0; i < 3; ++i)
+        for (int c = 0; c < 2; ++c)
+            q[2 * i + c] = rV * ((double)B[3 * i] * A[c] + (double)B[3 * i + 1] * A[2 + c] +
+                                 (double)B[3 * i + 2] * A[4 + c]);
+    const double rho2 = q[0] * q[0] + q[2] * q[2];
+    const double ir = rsqrt_f64(rho2);
+    cs[0] = rho2 > 0.0 ? q[0] * ir : 1.0;
+    cs[1] = rho2 > 0.0 ? q[2] * ir : 0.0;
+    r[0] = cs[0] * q[0] + cs[1] * q[2];
+    r[1] = cs[0] * q[1] + cs[1] * q[3];
+    r[2] = cs[0] * q[3] - cs[1] * q[1];
+    r[3] = q[4];
+    r[4] = q[5];
+}
+
 // Screen extent along one image axis (normalised coordinate u = x/z) of the
 // ellipsoid {(x-m)^T S^-1 (x-m) <= 1}: roots of
 // (mz^2 - S22) u^2 - 2 (ma mz - Sa2) u + (ma^2 - Saa) = 0.  The discriminant is
@@ -571,16 +607,30 @@ __global__ __launch_bounds__(256) void preprocess_kernel(RenderParams rp, Buffer
                                         (float)(0.5 * kLog2e * C11), 0.0f);
                     gp[4] = make_float4(0.0f, 0.0f, op, 0.0f);
                 } else {
-                    gp[2] = make_float4(Q11, A[0], A[2], A[4]);
-                    gp[3] = make_float4(A[1], A[3], A[5], v0[0]);
                     // near-plane segment: every ray that can reach alpha_min passes
                     // within sqrt(D2max) smax of the mean, so its closest point lies
                     // beyond depth mz - sqrt(D2max) smax, and beta <= smax: with
                     // (mz - znear) / smax - sqrt(D2max) > 6, Phi > 1 - 1e-9 there
                     const bool near = rp.near_segment &&
                                       (mz - vi.znear) / smax - sqrtf(D2max) <= 6.0f;
-                    gp[4] = make_float4(v0[1], v0[2], near ? -(K * kLog2e) : K * kLog2e,
-                                        epan ? mz * mz : (0.5f * kLog2e) * mz * mz);
+                    const float Ks = near ? -(K * kLog2e) : K * kLog2e;
+                    const float se = epan ? mz * mz : (0.5f * kLog2e) * mz * mz;
+                    if (DEG == 0 && raster_xray(rp)) {   // uniform (X-ray mode runs as DEG 0)
+                        double r[5], cs[2], rV;
+                        ray_axes(v0, A, r, cs, rV);
+                        const double e = mzd * mzd * ((double)v0[0] * v0[0] + (double)v0[1] * v0[1] +
+                                                      (double)v0[2] * v0[2]);
+                        gp[1] = make_float4((float)r[0], (float)r[1], (float)r[2], 0.0f);
+                        gp[2] = make_float4((float)r[3], (float)r[4], (float)(Ks * rV),
+                                            (float)(epan ? e : 0.5 * 1.4426950408889634 * e));
+                        gp[3] = make_float4(A[0], A[2], A[4], A[1]);
+                        gp[4] = make_float4(A[3], A[5], v0[0], v0[1]);
+                        gp[5] = make_float4(v0[2], Ks, se, mz);
+                    } else {
+                        gp[2] = make_float4(Q11, A[0], A[2], A[4]);
+                        gp[3] = make_float4(A[1], A[3], A[5], v0[0]);
+                        gp[4] = make_float4(v0[1], v0[2], Ks, se);
+                    }
                 }
                 gp[6] = make_float4(cr.cx, cr.cy, cr.a, cr.P);
                 gp[7] = make_float4(cr.R, cr.ymax, cr.yl, cr.on);
@@ -602,7 +652,7 @@ __global__ __launch_bounds__(256) void preprocess_kernel(RenderParams rp, Buffer
                         rgb[ch] = act_fwd(rp.act, acc);
                     }
                 }
-                gp[5] = make_float4(rgb[0], rgb[1], rgb[2], mz);
+                if (DEG != 0 || !raster_xray(rp)) gp[5] = make_float4(rgb[0], rgb[1], rgb[2], mz);
             }
         }
         if (count == 0) key = 0xFFFFFFFFu;
@@ -1159,10 +1209,10 @@ __device__ inline void splat_view_grad(const GaussView &g, const float *s, const
 }
 
 // The rasteriser's moments in the ray frame (raster_quad.hip: basis ray_frame of
-// v0/|v0|, slot 5 holding sum t - M_22, slots 6-8 Z over sqrt(E) with the signs of
+// v0/|v0|, in X-ray mode turned as in ray_axes; slot 5 holding sum t - M_22, slots 6-8 Z over sqrt(E) with the signs of
 // its first two taken out) to M, Z and U in the L-frame.
-__device__ inline void ray_to_lframe(const MeanRay &ray, const float *gr, float *Mm, float *Zm,
-                                     float *U)
+__device__ inline void ray_to_lframe(const MeanRay &ray, const GaussView &g, const ViewInfo &vi,
+                                     bool xray, const float *gr, float *Mm, float *Zm, float *U)
 {
     const float x = ray.v0[0], y = ray.v0[1], z = ray.v0[2];
     const float V2 = __fmaf_rn(x, x, __fmaf_rn(y, y, z * z));
@@ -1170,6 +1220,19 @@ __device__ inline void ray_to_lframe(const MeanRay &ray, const float *gr, float 
     const float e = (float)ray.mz * (V2 * iV);   // sqrt(E) = |L m|
     float B[9];
     ray_frame(x * iV, y * iV, z * iV, B);
+    if (xray) {   // uniform
+        const float ifx = 1.0f / vi.fx, ify = 1.0f / vi.fy;
+        const float A[6] = { g.L[0] * ifx, g.L[1] * ify, g.L[3] * ifx, g.L[4] * ify,
+                             g.L[6] * ifx, g.L[7] * ify };
+        double r[5], cs[2], rV;
+        ray_axes(ray.v0, A, r, cs, rV);
+        const float c = (float)cs[0], s = (float)cs[1];
+        for (int k = 0; k < 3; ++k) {
+            const float e0 = B[k], e1 = B[3 + k];
+            B[k] = fmaf(c, e0, s * e1);
+            B[3 + k] = fmaf(c, e1, -(s * e0));
+        }
+    }
     const float M[9] = { gr[0], gr[1], gr[2], gr[1], gr[3], gr[4], gr[2], gr[4], gr[9] - gr[5] };
     const float Z[3] = { -e * gr[6], -e * gr[7], e * gr[8] };
     const float Ur[3] = { gr[13], gr[14], gr[15] };
@@ -1255,7 +1318,8 @@ __global__ __launch_bounds__(128) void preprocess_bwd_kernel(
         float Mm[6] = { gr[0], gr[1], gr[2], gr[3], gr[4], gr[5] };
         float Zm[3] = { gr[6], gr[7], gr[8] };
         float U[3] = { gr[13], gr[14], gr[15] };
-        if (rp.ray_moments) ray_to_lframe(mean_ray(vi, mu, g), gr, Mm, Zm, U);   // uniform
+        if (rp.ray_moments)   // uniform
+            ray_to_lframe(mean_ray(vi, mu, g), g, vi, DEG == 0 && raster_xray(rp), gr, Mm, Zm, U);
         if (rp.near_segment) {
             Mm[0] -= 2.0f * g.p[0] * U[0];
             Mm[1] -= g.p[0] * U[1] + U[0] * g.p[1];

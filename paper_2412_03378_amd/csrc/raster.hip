@@ -1,26 +1,23 @@
-// Tile rasteriser, forward and backward, for gfx950 (wave64): X-ray mode, the
-// splatting opacity and the per-pixel window.  The colour modes with the volumetric
-// opacity are in raster_quad.hip, which shares the forward walk (raster_walk.h).
+// Tile rasteriser, forward and backward, for gfx950 (wave64): the splatting opacity and
+// the per-pixel window.  The colour modes with the volumetric opacity are in
+// raster_quad.hip, which shares the forward walk (raster_walk.h), X-ray mode is in
+// raster_xray.hip.
 //
 // One wave (64 lanes) owns one screen tile of TW x TH pixels; lane l holds the
 // TW*TH/64 pixels of column l % TW, rows l / TW + k * (64 / TW) ("slot" k).
 // Tiles are launched in the order of b.tile_order (heaviest lists first).
 // The tile's depth-sorted Gaussian list is walked in batches of B records
 // (B = 64 or 32, the block shape the autotuner picks with the tile shape)
-// staged in LDS (structure of arrays).  The colour forward (and the X-ray
-// forward with one pixel per lane) pre-tests the whole batch with broadcast
-// reads and then lets every lane evaluate its own passing records in order
-// (per-lane reads), so that an evaluation step is not spent on lanes whose
-// pixel the record misses; it keeps each lane's pass mask of the batch for
-// the backward.  The X-ray forward with several pixels per lane walks the
-// batch together, reading the three float4 of the bound pre-test first and
-// the other three only when some pixel of the slot passes.  The backward
-// reduces its per-pair gradients per Gaussian, so lanes that share a record
-// walk together: with the per-pixel window (8x8 tiles) each 4x4 quarter of the
-// tile (16 lanes) walks the records its own pixels' masks name, four records
-// per step; elsewhere the whole wave walks the records that the union of the
-// lanes' masks names, or, where the forward kept no masks, pre-tests each
-// record as the X-ray forward does.
+// staged in LDS (structure of arrays).  The forward pre-tests the whole batch
+// with broadcast reads and then lets every lane evaluate its own passing
+// records in order (per-lane reads), so that an evaluation step is not spent
+// on lanes whose pixel the record misses; it keeps each lane's pass mask of
+// the batch for the backward.  The backward reduces its per-pair gradients per
+// Gaussian, so lanes that share a record walk together: with the per-pixel
+// window (8x8 tiles) each 4x4 quarter of the tile (16 lanes) walks the records
+// its own pixels' masks name, four records per step; with the splatting
+// opacity the whole wave walks the records that the union of the lanes' masks
+// names.
 //
 // Per (pixel, Gaussian) pair, with the record (centre h + l, A, v0, mz, K',
 // bound form Q, l; see vgr_internal.h) and d = pixel centre - h - l:
@@ -35,7 +32,6 @@
 // under one wave-uniform branch per slot (taken when any lane's pixel in the
 // slot passes), with per-lane selects instead of nested execution masks.
 // The wave leaves its list as soon as every one of its pixels has stopped.
-// X-ray mode sums y over the whole list instead (Sec. 6.2).
 //
 // The backward walks each pixel's list in reverse from its last blended
 // Gaussian, recovering T in front of Gaussian i as T_after / (1 - alpha_i)
@@ -60,64 +56,9 @@ __global__ __launch_bounds__(64) void raster_fwd_kernel(RenderParams rp, Buffers
     walk_tile_fwd<TW, TH, MODE, COUNT, B>(rp, b, st, (int)b.tile_order[blockIdx.x], 0, blockIdx.x);
 }
 
-// Sum v[0..15] over the 64 lanes (transpose-reduce).  Afterwards lane l with
-// (l & 3) == 0 holds the total of index l / 4.
-//   step 1: v_permlane32_swap pairs (v[k], v[k+8]); after the add, lanes 0-31
-//           hold index k and lanes 32-63 index k + 8;
-//   step 2: v_permlane16_swap pairs (v[k], v[k+4]); row r (16 lanes) now
-//           holds indices 4 r + k, k = 0..3;
-//   step 3: lanes l and l ^ 8 (DPP row rotate by 8) keep one pair of indices
-//           each and send the other;
-//   step 4: lanes l and 7 - l of each 8-lane half row (DPP half mirror) keep
-//           one index each and send the other;
-//   step 5: sums within each quad (DPP quad permutations).
 constexpr int kDppRowRor4 = 0x124;
 constexpr int kDppRowRor2 = 0x122;
 constexpr int kDppRowRor1 = 0x121;
-
-// Index of the total lane l holds after wave_reduce16 (lanes l & 3 == 0).
-template <bool N13>
-__device__ __forceinline__ int wave_index(int lane)
-{
-    return N13 ? n13_index((lane >> 2) & 7, (lane >> 5) & 1) : lane >> 2;
-}
-
-// Steps 3 and 4 of wave_reduce16 as DPP adds with bank masks, each lane
-// writing the sum of the slot it keeps: across l ^ 8 the lanes of banks 0-1 of
-// each row keep slot 0 or 1 and those of banks 2-3 slot 2 or 3; across the
-// half-row mirror (7 - i within each 8 lanes) banks 0 and 2 keep the first
-// and banks 1 and 3 the second.  The compiler forms DPP adds only with every
-// bank enabled and then routes the slots with selects.  The s_nops give the
-// two wait states a DPP read needs after a VALU write of its source VGPR.
-__device__ __forceinline__ float wave_steps34(float v0, float v1, float v2, float v3)
-{
-    float r0, r1, out;
-    asm volatile(
-        "s_nop 1\n\t"
-        "v_add_f32_dpp %1, %3, %3 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
-        "v_add_f32_dpp %1, %5, %5 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
-        "v_add_f32_dpp %2, %4, %4 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
-        "v_add_f32_dpp %2, %6, %6 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
-        "v_add_f32_dpp %0, %1, %1 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
-        "s_nop 0\n\t"
-        "v_add_f32_dpp %0, %2, %2 row_half_mirror row_mask:0xf bank_mask:0xa"
-        : "=&v"(out), "=&v"(r0), "=&v"(r1)
-        : "v"(v0), "v"(v1), "v"(v2), "v"(v3));
-    return out;
-}
-
-template <bool N13>
-__device__ __forceinline__ float wave_reduce16(float (&v)[16], int lane)
-{
-    (void)lane;
-    pair_step1<N13>(v, [](float a, float b) { return swap_add32(a, b); });
-#pragma unroll
-    for (int k = 0; k < 4; ++k) v[k] = swap_add16(v[k], v[k + 4]);
-    v[0] = wave_steps34(v[0], v[1], v[2], v[3]);
-    v[0] += dpp_move<kDppQuadXor2>(v[0]);
-    v[0] += dpp_move<kDppQuadXor1>(v[0]);
-    return v[0];
-}
 
 // 8x8 tiles, one pixel per lane (x = lane bits 0-2, y = lane bits 3-5): the
 // 4x4 quarter of lane l is (l bit 2, l bit 5).  Sum v[0..15] over the 16
@@ -198,19 +139,16 @@ __global__ __launch_bounds__(64) void raster_bwd_kernel(RenderParams rp, Buffers
     static_assert(B == 32 || B == 64, "records per batch");
     constexpr int PPL = TileMap<TW, TH>::PPL;
     constexpr int RS = TileMap<TW, TH>::RS;
-    constexpr bool COLOR = MODE != VGR_MODE_XRAY && MODE != kModeXrayNear && MODE != kModeXrayEpan;
     constexpr bool SPLAT = MODE == kModeSplat;   // colour with the 3DGS splatting alpha
-    constexpr bool NEAR = MODE == kModeColorNear || MODE == kModeXrayNear;
-    constexpr bool EPAN = MODE == kModeColorEpan || MODE == kModeXrayEpan;
-    constexpr int NCH = COLOR ? 3 : 1;
-    // the forward kept its pre-test masks for this shape and mode
-    constexpr bool KEEP = COLOR || PPL == 1;
+    constexpr bool NEAR = MODE == kModeColorNear;
+    constexpr bool EPAN = MODE == kModeColorEpan;
+    constexpr int NCH = 3;
     // per-pixel window (8x8 tiles): each 4x4 quarter walks the records of its own
     // pixels, so that one step of the wave handles up to four records
-    // (quarter_reduce16); the splatting opacity's and the X-ray backward's few
-    // operations per pair do not pay for the per-lane walk (measured slower)
+    // (quarter_reduce16); the splatting opacity's few operations per pair do not pay
+    // for the per-lane walk (measured slower)
     constexpr bool QUAD = WIN;
-    static_assert(!WIN || (PPL == 1 && COLOR && !SPLAT), "the window's tiles and modes");
+    static_assert(WIN != SPLAT && (!WIN || PPL == 1), "splatting opacity, or the window on 8x8 tiles");
     __shared__ Stage<B> st;
 
     const bool timed = b.wg_time != nullptr;   // uniform
@@ -350,37 +288,15 @@ __global__ __launch_bounds__(64) void raster_bwd_kernel(RenderParams rp, Buffers
             if (COUNT) n.blend += bl ? 1u : 0u;
             const uint64_t bm = __builtin_amdgcn_ballot_w64(!(y < tau2)) & pm;
             if (bm == 0) continue;                      // wave-uniform
-            float dy_;
-            if constexpr (WIN) {
-                // per-pixel window: the forward's masks name only composited
-                // pairs, whose dL/dy and alpha T_before the replay left
-                float2 wv = make_float2(0.0f, 0.0f);
-                if (bl) wv = b.wpair[(size_t)jpos * 64 + lane];
-                const float wgt = bl ? wv.y : 0.0f;
-                acc[10] = __fmaf_rn(g[k][0], wgt, acc[10]);
-                acc[11] = __fmaf_rn(g[k][1], wgt, acc[11]);
-                acc[12] = __fmaf_rn(g[k][2], wgt, acc[12]);
-                dy_ = bl ? wv.x : 0.0f;
-            } else if constexpr (COLOR) {
-                const bool clamped = y > ymax;
-                const float om = fast_exp2(-(clamped ? ymax : y));
-                const float inv = fast_rcp(om);
-                const float alpha = 1.0f - om;
-                const float Tb = T[k] * inv;
-                // dL/dalpha = T_before (g.c) - (g.B) / (1 - alpha)
-                const float gc = __fmaf_rn(g[k][0], fr.c0,
-                                           __fmaf_rn(g[k][1], fr.c1, g[k][2] * fr.c2));
-                const float da = __fmaf_rn(Tb, gc, -(inv * GB[k]));
-                const float wgt = bl ? alpha * Tb : 0.0f;
-                acc[10] = __fmaf_rn(g[k][0], wgt, acc[10]);
-                acc[11] = __fmaf_rn(g[k][1], wgt, acc[11]);
-                acc[12] = __fmaf_rn(g[k][2], wgt, acc[12]);
-                GB[k] = __fmaf_rn(gc, wgt, GB[k]);
-                T[k] = bl ? Tb : T[k];
-                dy_ = (bl && !clamped) ? da * kLn2 * om : 0.0f;
-            } else {
-                dy_ = bl ? g[k][0] * kLn2 : 0.0f;
-            }
+            // per-pixel window: the forward's masks name only composited
+            // pairs, whose dL/dy and alpha T_before the replay left
+            float2 wv = make_float2(0.0f, 0.0f);
+            if (bl) wv = b.wpair[(size_t)jpos * 64 + lane];
+            const float wgt = bl ? wv.y : 0.0f;
+            acc[10] = __fmaf_rn(g[k][0], wgt, acc[10]);
+            acc[11] = __fmaf_rn(g[k][1], wgt, acc[11]);
+            acc[12] = __fmaf_rn(g[k][2], wgt, acc[12]);
+            const float dy_ = bl ? wv.x : 0.0f;
             touched |= bm;
             // t = dL/d(ln x) = dL/dy * y (selected, not multiplied, to zero
             // for lanes that do not blend); since ln x is ln K' plus terms
@@ -440,110 +356,79 @@ __global__ __launch_bounds__(64) void raster_bwd_kernel(RenderParams rp, Buffers
         }
     };
 
-    if constexpr (KEEP) {
-        // Batches aligned as in the forward, whose pre-test masks are reused:
-        // the walk visits only records some pixel of the tile admits.
-        for (int bs = (int)range.x + ((maxlast - (int)range.x) / B) * B; bs >= (int)range.x;
-             bs -= B) {
-            const int j = bs + lane;
-            if (lane < B && j <= maxlast) stage_record(st, b, lane, b.inst_val[j]);
-            uint64_t mask[PPL];
-            uint64_t any = 0;
+    // Batches aligned as in the forward, whose pre-test masks are reused:
+    // the walk visits only records some pixel of the tile admits.
+    for (int bs = (int)range.x + ((maxlast - (int)range.x) / B) * B; bs >= (int)range.x;
+         bs -= B) {
+        const int j = bs + lane;
+        if (lane < B && j <= maxlast) stage_record(st, b, lane, b.inst_val[j]);
+        uint64_t mask[PPL];
+        uint64_t any = 0;
 #pragma unroll
-            for (int k = 0; k < PPL; ++k) {
-                // records of the batch up to the pixel's last blended one
-                const int d = last[k] - bs;
-                const uint64_t lim = d < 0 ? 0ull : (d >= 63 ? ~0ull : (2ull << d) - 1ull);
-                mask[k] = b.pmask[mask_word<B>((uint32_t)bs, gt, lane) * PPL + k] & lim;
-                any |= mask[k];
-            }
-            if constexpr (QUAD) {
-                // the records some pixel of the lane's quarter admits, walked
-                // from the back; a quarter with none left idles on record 0
-                // (staged, so its arithmetic stays finite) with no pixel passing
-                // (bit-reversed masks: the next record is the lowest set bit)
-                uint64_t ur = __builtin_bitreverse64(quarter_or(any));
-                const uint64_t mr = __builtin_bitreverse64(mask[0]);
-                __syncthreads();
-                bool act = ur != 0;
-                if (wave_any(act)) do {
-                    const int jr = act ? __builtin_ctzll(ur) : 63;
-                    const int qi = 63 - jr;
-                    ur &= ur - 1ull;
-                    if (COUNT) {
-                        n.visits += lane == 0 ? 1u : 0u;
-                        n.visits_full += (act && (lane & 0x1B) == 0) ? 1u : 0u;
-                    }
-                    const RecRegs rr = load_regs(st, qi);
-                    const PreRec pr = pre_of(rr);
-                    const float dx = (pxc - pr.hx) - pr.lx;
-                    bool pass[PPL];
-                    pass[0] = act && ((mr >> jr) & 1u);
-                    record(qi, pr, dx, pass, bs + qi);
-                    act = ur != 0;
-                } while (wave_any(act));
-                __syncthreads();
-                continue;
-            }
-            // union over the wave: OR within each row of 16 lanes, then of the rows
-            uint32_t lo = (uint32_t)any, hi = (uint32_t)(any >> 32);
-            lo |= dpp_move_u<kDppRowRor8>(lo);
-            hi |= dpp_move_u<kDppRowRor8>(hi);
-            lo |= dpp_move_u<kDppRowRor4>(lo);
-            hi |= dpp_move_u<kDppRowRor4>(hi);
-            lo |= dpp_move_u<kDppRowRor2>(lo);
-            hi |= dpp_move_u<kDppRowRor2>(hi);
-            lo |= dpp_move_u<kDppRowRor1>(lo);
-            hi |= dpp_move_u<kDppRowRor1>(hi);
-            const uint32_t ulo = __builtin_amdgcn_readlane(lo, 0) | __builtin_amdgcn_readlane(lo, 16) |
-                                 __builtin_amdgcn_readlane(lo, 32) | __builtin_amdgcn_readlane(lo, 48);
-            const uint32_t uhi = __builtin_amdgcn_readlane(hi, 0) | __builtin_amdgcn_readlane(hi, 16) |
-                                 __builtin_amdgcn_readlane(hi, 32) | __builtin_amdgcn_readlane(hi, 48);
-            uint64_t u = ((uint64_t)uhi << 32) | ulo;   // wave-uniform
+        for (int k = 0; k < PPL; ++k) {
+            // records of the batch up to the pixel's last blended one
+            const int d = last[k] - bs;
+            const uint64_t lim = d < 0 ? 0ull : (d >= 63 ? ~0ull : (2ull << d) - 1ull);
+            mask[k] = b.pmask[mask_word<B>((uint32_t)bs, gt, lane) * PPL + k] & lim;
+            any |= mask[k];
+        }
+        if constexpr (QUAD) {
+            // the records some pixel of the lane's quarter admits, walked
+            // from the back; a quarter with none left idles on record 0
+            // (staged, so its arithmetic stays finite) with no pixel passing
+            // (bit-reversed masks: the next record is the lowest set bit)
+            uint64_t ur = __builtin_bitreverse64(quarter_or(any));
+            const uint64_t mr = __builtin_bitreverse64(mask[0]);
             __syncthreads();
-            while (u != 0) {
-                const int qi = 63 - __builtin_clzll(u);
-                u &= ~(1ull << qi);
-                if (COUNT) n.visits += lane == 0 ? 1u : 0u;
+            bool act = ur != 0;
+            if (wave_any(act)) do {
+                const int jr = act ? __builtin_ctzll(ur) : 63;
+                const int qi = 63 - jr;
+                ur &= ur - 1ull;
+                if (COUNT) {
+                    n.visits += lane == 0 ? 1u : 0u;
+                    n.visits_full += (act && (lane & 0x1B) == 0) ? 1u : 0u;
+                }
                 const RecRegs rr = load_regs(st, qi);
                 const PreRec pr = pre_of(rr);
                 const float dx = (pxc - pr.hx) - pr.lx;
                 bool pass[PPL];
-#pragma unroll
-                for (int k = 0; k < PPL; ++k) pass[k] = (mask[k] >> qi) & 1u;
+                pass[0] = act && ((mr >> jr) & 1u);
                 record(qi, pr, dx, pass, bs + qi);
-            }
+                act = ur != 0;
+            } while (wave_any(act));
             __syncthreads();
+            continue;
         }
-    } else {
-        for (int be = maxlast + 1; be > (int)range.x; be -= B) {
-            const int bs = max((int)range.x, be - B);
-            const int j = bs + lane;
-            if (lane < B && j < be) stage_record(st, b, lane, b.inst_val[j]);
-            __syncthreads();
-            for (int qi = be - 1 - bs; qi >= 0; --qi) {
-                const int jpos = bs + qi;
-                const PreRec pr = load_pre(st, qi);
-                const ColTerms ct = col_terms(pr, pxc);
-                bool pass[PPL];
-                bool anyp = false;
+        // union over the wave: OR within each row of 16 lanes, then of the rows
+        uint32_t lo = (uint32_t)any, hi = (uint32_t)(any >> 32);
+        lo |= dpp_move_u<kDppRowRor8>(lo);
+        hi |= dpp_move_u<kDppRowRor8>(hi);
+        lo |= dpp_move_u<kDppRowRor4>(lo);
+        hi |= dpp_move_u<kDppRowRor4>(hi);
+        lo |= dpp_move_u<kDppRowRor2>(lo);
+        hi |= dpp_move_u<kDppRowRor2>(hi);
+        lo |= dpp_move_u<kDppRowRor1>(lo);
+        hi |= dpp_move_u<kDppRowRor1>(hi);
+        const uint32_t ulo = __builtin_amdgcn_readlane(lo, 0) | __builtin_amdgcn_readlane(lo, 16) |
+                             __builtin_amdgcn_readlane(lo, 32) | __builtin_amdgcn_readlane(lo, 48);
+        const uint32_t uhi = __builtin_amdgcn_readlane(hi, 0) | __builtin_amdgcn_readlane(hi, 16) |
+                             __builtin_amdgcn_readlane(hi, 32) | __builtin_amdgcn_readlane(hi, 48);
+        uint64_t u = ((uint64_t)uhi << 32) | ulo;   // wave-uniform
+        __syncthreads();
+        while (u != 0) {
+            const int qi = 63 - __builtin_clzll(u);
+            u &= ~(1ull << qi);
+            if (COUNT) n.visits += lane == 0 ? 1u : 0u;
+            const RecRegs rr = load_regs(st, qi);
+            const PreRec pr = pre_of(rr);
+            const float dx = (pxc - pr.hx) - pr.lx;
+            bool pass[PPL];
 #pragma unroll
-                for (int k = 0; k < PPL; ++k) {
-                    float dy;
-                    const bool inl = jpos <= last[k];
-                    pass[k] = inl && pre_test(pr, ct, pyc[k], dy);
-                    anyp |= pass[k];
-                    if (COUNT) {
-                        n.test += inl ? 1u : 0u;
-                        const bool anyl = wave_any(inl);
-                        n.visits += (lane == 0 && anyl) ? 1u : 0u;
-                    }
-                }
-                if (!wave_any(anyp)) continue;             // wave-uniform
-                record(qi, pr, ct.dx, pass, jpos);
-            }
-            __syncthreads();
+            for (int k = 0; k < PPL; ++k) pass[k] = (mask[k] >> qi) & 1u;
+            record(qi, pr, dx, pass, bs + qi);
         }
+        __syncthreads();
     }
     if (COUNT) {
         atomicAdd(&b.counters[8], (unsigned long long)n.test);
@@ -891,19 +776,8 @@ template <int TW, int TH, int B>
 hipError_t fwd_shape(const RenderParams &rp, const Buffers &b, bool count, hipStream_t s)
 {
     const dim3 grid(rp.total_tiles), block(64);
-    if (rp.alpha_model == VGR_ALPHA_SPLAT) {
-        if (count) raster_fwd_kernel<TW, TH, kModeSplat, true, B><<<grid, block, 0, s>>>(rp, b);
-        else raster_fwd_kernel<TW, TH, kModeSplat, false, B><<<grid, block, 0, s>>>(rp, b);
-    } else if (rp.kernel == VGR_KERNEL_EPANECHNIKOV) {
-        if (count) raster_fwd_kernel<TW, TH, kModeXrayEpan, true, B><<<grid, block, 0, s>>>(rp, b);
-        else raster_fwd_kernel<TW, TH, kModeXrayEpan, false, B><<<grid, block, 0, s>>>(rp, b);
-    } else if (rp.near_segment) {
-        if (count) raster_fwd_kernel<TW, TH, kModeXrayNear, true, B><<<grid, block, 0, s>>>(rp, b);
-        else raster_fwd_kernel<TW, TH, kModeXrayNear, false, B><<<grid, block, 0, s>>>(rp, b);
-    } else {
-        if (count) raster_fwd_kernel<TW, TH, VGR_MODE_XRAY, true, B><<<grid, block, 0, s>>>(rp, b);
-        else raster_fwd_kernel<TW, TH, VGR_MODE_XRAY, false, B><<<grid, block, 0, s>>>(rp, b);
-    }
+    if (count) raster_fwd_kernel<TW, TH, kModeSplat, true, B><<<grid, block, 0, s>>>(rp, b);
+    else raster_fwd_kernel<TW, TH, kModeSplat, false, B><<<grid, block, 0, s>>>(rp, b);
     return hipGetLastError();
 }
 
@@ -911,25 +785,10 @@ template <int TW, int TH, int B>
 hipError_t bwd_shape(const RenderParams &rp, const Buffers &b, bool count, hipStream_t s)
 {
     const dim3 grid(rp.total_tiles), block(64);
-    if (rp.alpha_model == VGR_ALPHA_SPLAT) {
-        if (count) raster_bwd_kernel<TW, TH, kModeSplat, true, B><<<grid, block, 0, s>>>(rp, b);
-        else raster_bwd_kernel<TW, TH, kModeSplat, false, B><<<grid, block, 0, s>>>(rp, b);
-    } else if (rp.kernel == VGR_KERNEL_EPANECHNIKOV) {
-        if (count) raster_bwd_kernel<TW, TH, kModeXrayEpan, true, B><<<grid, block, 0, s>>>(rp, b);
-        else raster_bwd_kernel<TW, TH, kModeXrayEpan, false, B><<<grid, block, 0, s>>>(rp, b);
-    } else if (rp.near_segment) {
-        if (count) raster_bwd_kernel<TW, TH, kModeXrayNear, true, B><<<grid, block, 0, s>>>(rp, b);
-        else raster_bwd_kernel<TW, TH, kModeXrayNear, false, B><<<grid, block, 0, s>>>(rp, b);
-    } else {
-        if (count) raster_bwd_kernel<TW, TH, VGR_MODE_XRAY, true, B><<<grid, block, 0, s>>>(rp, b);
-        else raster_bwd_kernel<TW, TH, VGR_MODE_XRAY, false, B><<<grid, block, 0, s>>>(rp, b);
-    }
+    if (count) raster_bwd_kernel<TW, TH, kModeSplat, true, B><<<grid, block, 0, s>>>(rp, b);
+    else raster_bwd_kernel<TW, TH, kModeSplat, false, B><<<grid, block, 0, s>>>(rp, b);
     return hipGetLastError();
 }
-
-}  // namespace
-
-namespace {
 
 template <int B>
 hipError_t fwd_batch(const RenderParams &rp, const Buffers &b, bool count, hipStream_t s)
@@ -961,6 +820,7 @@ hipError_t launch_raster_fwd(const RenderParams &rp, const Buffers &b, bool coun
     if (rp.total_tiles <= 0) return hipSuccess;
     if (rp.pixel_window > 0) return window_fwd(rp, b, s);
     if (raster_quads(rp)) return launch_color_fwd(rp, b, count, s);
+    if (raster_xray(rp)) return launch_xray(rp, b, true, count, s);
     return rp.batch == 32 ? fwd_batch<32>(rp, b, count, s) : fwd_batch<64>(rp, b, count, s);
 }
 
@@ -969,6 +829,7 @@ hipError_t launch_raster_bwd(const RenderParams &rp, const Buffers &b, bool coun
     if (rp.total_tiles <= 0) return hipSuccess;
     if (rp.pixel_window > 0) return window_bwd(rp, b, s);
     if (raster_quads(rp)) return launch_color_bwd(rp, b, count, s);
+    if (raster_xray(rp)) return launch_xray(rp, b, false, count, s);
     return rp.batch == 32 ? bwd_batch<32>(rp, b, count, s) : bwd_batch<64>(rp, b, count, s);
 }
 

@@ -76,6 +76,13 @@ __device__ __forceinline__ float swap_add16(float a, float b)
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// LDS stores of this wave visible to its own lanes.
+__device__ __forceinline__ void lds_wave_sync()
+{
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // DPP lane moves (gfx9 encodings): row rotate right by 8, quad permutations
 // [2,3,0,1] and [1,0,3,2].
 constexpr int kDppRowRor8 = 0x128;
@@ -156,6 +163,61 @@ __device__ __forceinline__ void pair_add8x4(float (&v)[16])
     v[3] = r3;
 }
 #undef VGR_PAIR_ADD8
+
+// Sum v[0..15] over the 64 lanes (transpose-reduce).  Afterwards lane l with
+// (l & 3) == 0 holds the total of index l / 4.
+//   step 1: v_permlane32_swap pairs (v[k], v[k+8]); after the add, lanes 0-31
+//           hold index k and lanes 32-63 index k + 8;
+//   step 2: v_permlane16_swap pairs (v[k], v[k+4]); row r (16 lanes) now
+//           holds indices 4 r + k, k = 0..3;
+//   step 3: lanes l and l ^ 8 (DPP row rotate by 8) keep one pair of indices
+//           each and send the other;
+//   step 4: lanes l and 7 - l of each 8-lane half row (DPP half mirror) keep
+//           one index each and send the other;
+//   step 5: sums within each quad (DPP quad permutations).
+// Index of the total lane l holds after wave_reduce16 (lanes l & 3 == 0).
+template <bool N13>
+__device__ __forceinline__ int wave_index(int lane)
+{
+    return N13 ? n13_index((lane >> 2) & 7, (lane >> 5) & 1) : lane >> 2;
+}
+
+// Steps 3 and 4 of wave_reduce16 as DPP adds with bank masks, each lane
+// writing the sum of the slot it keeps: across l ^ 8 the lanes of banks 0-1 of
+// each row keep slot 0 or 1 and those of banks 2-3 slot 2 or 3; across the
+// half-row mirror (7 - i within each 8 lanes) banks 0 and 2 keep the first
+// and banks 1 and 3 the second.  The compiler forms DPP adds only with every
+// bank enabled and then routes the slots with selects.  The s_nops give the
+// two wait states a DPP read needs after a VALU write of its source VGPR.
+__device__ __forceinline__ float wave_steps34(float v0, float v1, float v2, float v3)
+{
+    float r0, r1, out;
+    asm volatile(
+        "s_nop 1\n\t"
+        "v_add_f32_dpp %1, %3, %3 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+        "v_add_f32_dpp %1, %5, %5 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %2, %4, %4 row_ror:8 row_mask:0xf bank_mask:0x3\n\t"
+        "v_add_f32_dpp %2, %6, %6 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+        "v_add_f32_dpp %0, %1, %1 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+        "s_nop 0\n\t"
+        "v_add_f32_dpp %0, %2, %2 row_half_mirror row_mask:0xf bank_mask:0xa"
+        : "=&v"(out), "=&v"(r0), "=&v"(r1)
+        : "v"(v0), "v"(v1), "v"(v2), "v"(v3));
+    return out;
+}
+
+template <bool N13>
+__device__ __forceinline__ float wave_reduce16(float (&v)[16], int lane)
+{
+    (void)lane;
+    pair_step1<N13>(v, [](float a, float b) { return swap_add32(a, b); });
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = swap_add16(v[k], v[k + 4]);
+    v[0] = wave_steps34(v[0], v[1], v[2], v[3]);
+    v[0] += dpp_move<kDppQuadXor2>(v[0]);
+    v[0] += dpp_move<kDppQuadXor1>(v[0]);
+    return v[0];
+}
 
 constexpr int kBlock = 4;        // pixel block side
 constexpr int kRegion = 8;       // region side: four blocks

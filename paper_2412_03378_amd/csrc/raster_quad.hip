@@ -82,13 +82,6 @@ __device__ __forceinline__ int log2_regions(const RenderParams &rp)
     return 31 - __builtin_clz((uint32_t)(rp.tile_w * rp.tile_h / (kRegion * kRegion)));
 }
 
-// LDS stores of this wave visible to its own lanes.
-__device__ __forceinline__ void lds_wave_sync()
-{
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_wave_barrier();
-}
-
 // Quad lane J's value on the quad's four lanes.  (bound_ctrl: every lane of the
 // permutation is valid, and with it the compiler folds the move into the user.)
 template <int J>

@@ -18,7 +18,7 @@ struct Stage {
 };
 
 // Word of the kept pre-test mask of lane `lane` for the batch that starts at
-// list position bs of global tile gt (layout: raster_keeps_masks).
+// list position bs of global tile gt (layout: pmask_words).
 template <int B>
 __device__ __forceinline__ size_t mask_word(uint32_t bs, int gt, int lane)
 {
@@ -214,12 +214,11 @@ __device__ __forceinline__ void walk_tile_fwd(const RenderParams &rp, const Buff
     static_assert(B == 32 || B == 64, "records per batch");
     constexpr int PPL = TileMap<TW, TH>::PPL;
     constexpr int RS = TileMap<TW, TH>::RS;
-    constexpr bool COLOR = MODE != VGR_MODE_XRAY && MODE != kModeXrayNear && MODE != kModeXrayEpan;
     constexpr bool SPLAT = MODE == kModeSplat;   // colour with the 3DGS splatting alpha
-    constexpr bool NEAR = MODE == kModeColorNear || MODE == kModeXrayNear;
-    constexpr bool EPAN = MODE == kModeColorEpan || MODE == kModeXrayEpan;
+    constexpr bool NEAR = MODE == kModeColorNear;
+    constexpr bool EPAN = MODE == kModeColorEpan;
     // the backward runs in 4x4 pixel blocks from the pairs blended here (qmask)
-    constexpr bool BLOCKS = COLOR && !SPLAT;
+    constexpr bool BLOCKS = !SPLAT;
     static_assert(!BLOCKS || (B == 64 && TW == 8 && TH == 8), "a region, 64 entries per batch");
     static_assert(BLOCKS || !CULL, "tiles are culled already");
     const bool timed = b.wg_time != nullptr;   // uniform
@@ -283,7 +282,7 @@ __device__ __forceinline__ void walk_tile_fwd(const RenderParams &rp, const Buff
         if (lane < B && j + B < range.y) item = b.inst_val[j + B];
         const bool bad = wave_any(wild);   // the batch's records pass the pre-test untested
         __syncthreads();
-        if constexpr (PPL == 1 || COLOR) {
+        {
             // Phase 1: bound pre-test of the whole batch (broadcast records);
             // bit q of mask[k] marks record q as passing for the lane's slot k.
             // The two 32-record halves fill 32-bit words with the sign bits of the
@@ -322,7 +321,7 @@ __device__ __forceinline__ void walk_tile_fwd(const RenderParams &rp, const Buff
             for (int k = 0; k < PPL; ++k)
                 mask[k] = __builtin_amdgcn_inverse_ballot_w64(alive[k])
                               ? ((uint64_t)mhalf[1][k] << 32) | mhalf[0][k] : 0ull;
-            // kept for the backward (layout: raster_keeps_masks)
+            // kept for the backward (layout: pmask_words)
             if constexpr (!BLOCKS) {
     #pragma unroll
                 for (int k = 0; k < PPL; ++k)
@@ -381,36 +380,29 @@ __device__ __forceinline__ void walk_tile_fwd(const RenderParams &rp, const Buff
                         om = fast_exp2(-(y > ymax ? ymax : y));
                         wa = 1.0f - om;
                     }
-                    if constexpr (COLOR) {
-                        const float Tn = T[k] * om;
-                        const uint64_t low = __builtin_amdgcn_ballot_w64(Tn < Tmin);
-                        const uint64_t dom = blm & ~low;
-                        const bool dob = __builtin_amdgcn_inverse_ballot_w64(dom);
-                        const float wgt = dob ? wa * T[k] : 0.0f;
-                        C0[k] = __fmaf_rn(fr.c0, wgt, C0[k]);
-                        C1[k] = __fmaf_rn(fr.c1, wgt, C1[k]);
-                        C2[k] = __fmaf_rn(fr.c2, wgt, C2[k]);
-                        T[k] = dob ? Tn : T[k];
-                        alive[k] &= ~(blm & low);
-                        if constexpr (BLOCKS) {
-                            mine |= (uint64_t)(dob ? 1u : 0u) << (entry & 63u);
-                            const uint64_t cl = __builtin_amdgcn_ballot_w64(y > ymax) & dom;
-                            if (__builtin_expect(cl != 0, 0)) {
-                                // (the empty asm keeps this a branch)
-                                uint32_t one = __builtin_amdgcn_inverse_ballot_w64(cl) ? 1u : 0u;
-                                asm volatile("" : "+v"(one));
-                                over |= (uint64_t)one << (entry & 63u);
-                            }
-                        } else {
-                            last[k] = dob ? (int)(bs + qi) : last[k];
+                    const float Tn = T[k] * om;
+                    const uint64_t low = __builtin_amdgcn_ballot_w64(Tn < Tmin);
+                    const uint64_t dom = blm & ~low;
+                    const bool dob = __builtin_amdgcn_inverse_ballot_w64(dom);
+                    const float wgt = dob ? wa * T[k] : 0.0f;
+                    C0[k] = __fmaf_rn(fr.c0, wgt, C0[k]);
+                    C1[k] = __fmaf_rn(fr.c1, wgt, C1[k]);
+                    C2[k] = __fmaf_rn(fr.c2, wgt, C2[k]);
+                    T[k] = dob ? Tn : T[k];
+                    alive[k] &= ~(blm & low);
+                    if constexpr (BLOCKS) {
+                        mine |= (uint64_t)(dob ? 1u : 0u) << (entry & 63u);
+                        const uint64_t cl = __builtin_amdgcn_ballot_w64(y > ymax) & dom;
+                        if (__builtin_expect(cl != 0, 0)) {
+                            // (the empty asm keeps this a branch)
+                            uint32_t one = __builtin_amdgcn_inverse_ballot_w64(cl) ? 1u : 0u;
+                            asm volatile("" : "+v"(one));
+                            over |= (uint64_t)one << (entry & 63u);
                         }
-                        if (COUNT) n.blend += dob ? 1u : 0u;
                     } else {
-                        const bool bl = __builtin_amdgcn_inverse_ballot_w64(blm);
-                        C0[k] += bl ? y : 0.0f;
-                        last[k] += bl ? 1 : 0;   // number of terms (starts at -1)
-                        if (COUNT) n.blend += bl ? 1u : 0u;
+                        last[k] = dob ? (int)(bs + qi) : last[k];
                     }
+                    if (COUNT) n.blend += dob ? 1u : 0u;
                     left = __builtin_amdgcn_ballot_w64(mk != 0) & alive[k];
                 } while (left != 0);
                 if constexpr (BLOCKS) {
@@ -423,52 +415,12 @@ __device__ __forceinline__ void walk_tile_fwd(const RenderParams &rp, const Buff
                     if (lane < 4) b.qflag[bq + lane] = flag;
                 }
             }
-        } else {
-            // X-ray with several pixels per lane: every record of the list is
-            // summed (no early stop), and one broadcast read per step is
-            // shared by the lane's pixels, which measured faster than a
-            // per-lane walk that re-reads the record for each pixel.
-            for (int qi = 0; qi < nb; ++qi) {
-                const PreRec pr = load_pre(st, qi);
-                const ColTerms ct = col_terms(pr, pxc);
-    #pragma unroll
-                for (int k = 0; k < PPL; ++k) {
-                    float dy;
-                    const bool near = pre_test(pr, ct, pyc[k], dy);   // always evaluated: sets dy
-                    const bool pass = __builtin_amdgcn_inverse_ballot_w64(alive[k]) && near;
-                    const bool anyp = wave_any(pass);
-                    if (COUNT) {
-                        n.test += __builtin_amdgcn_inverse_ballot_w64(alive[k]) ? 1u : 0u;
-                        n.visits += (lane == 0 && alive[k] != 0) ? 1u : 0u;
-                        n.visits_full += (lane == 0 && anyp) ? 1u : 0u;
-                    }
-                    if (!anyp) continue;                  // wave-uniform
-                    if (COUNT) n.full += pass ? 1u : 0u;
-                    const FullRec fr = load_full(st, qi);
-                    PairGeom g;
-                    pair_geom(pr, fr, ct.dx, dy, g);
-                    const float rq = fast_rsq(g.qw);
-                    const float ex = profile<EPAN>(fr.se, g.num, rq * rq);
-                    float y = (NEAR ? fabsf(fr.K) : fr.K) * un[k] * rq * ex;
-                    if constexpr (NEAR) {
-                        if (fr.K < 0.0f)
-                            y *= norm_cdf(near_eta(fr.v0x, fr.v0y, fr.v0z, fr.mz, g.w0, g.w1, g.w2,
-                                                   g.qw, rq, zn));
-                    }
-                    const bool bl = pass && !(y < tau2);
-                    C0[k] += bl ? y : 0.0f;
-                    last[k] += bl ? 1 : 0;   // number of terms (starts at -1)
-                    if (COUNT) n.blend += bl ? 1u : 0u;
-                }
-            }
         }
         __syncthreads();
-        if (COLOR) {
-            uint64_t any = 0;
+        uint64_t any = 0;
 #pragma unroll
-            for (int k = 0; k < PPL; ++k) any |= alive[k];
-            if (any == 0) break;                          // every pixel has stopped
-        }
+        for (int k = 0; k < PPL; ++k) any |= alive[k];
+        if (any == 0) break;                          // every pixel has stopped
     }
 
     const int64_t HW = (int64_t)W * H;
@@ -478,20 +430,13 @@ __device__ __forceinline__ void walk_tile_fwd(const RenderParams &rp, const Buff
         if (px < W && py < H) {
             const int64_t idx = (int64_t)py * W + px;
             const int64_t pidx = vi.pix_off + idx;
-            if (COLOR) {
-                vi.out[idx] = __fmaf_rn(T[k], rp.bg[0], C0[k]);
-                vi.out[HW + idx] = __fmaf_rn(T[k], rp.bg[1], C1[k]);
-                vi.out[2 * HW + idx] = __fmaf_rn(T[k], rp.bg[2], C2[k]);
-                b.T_final[pidx] = T[k];
-                if (!BLOCKS) b.last_pos[pidx] = last[k];
-                b.last_id[pidx] = last[k] >= 0
-                    ? (int32_t)((int64_t)b.inst_val[last[k]] - (int64_t)v * rp.n) : -1;
-            } else {
-                vi.out[idx] = C0[k] * kLn2;
-                b.T_final[pidx] = fast_exp2(-C0[k]);
-                b.last_pos[pidx] = (int32_t)range.y - 1;
-                b.last_id[pidx] = last[k] + 1;
-            }
+            vi.out[idx] = __fmaf_rn(T[k], rp.bg[0], C0[k]);
+            vi.out[HW + idx] = __fmaf_rn(T[k], rp.bg[1], C1[k]);
+            vi.out[2 * HW + idx] = __fmaf_rn(T[k], rp.bg[2], C2[k]);
+            b.T_final[pidx] = T[k];
+            if (!BLOCKS) b.last_pos[pidx] = last[k];
+            b.last_id[pidx] = last[k] >= 0
+                ? (int32_t)((int64_t)b.inst_val[last[k]] - (int64_t)v * rp.n) : -1;
         }
     }
     if (BLOCKS && lane < 4)

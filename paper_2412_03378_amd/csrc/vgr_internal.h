@@ -43,9 +43,12 @@ constexpr int kModeColorEpan = 5, kModeXrayEpan = 6;
 //                               K' < 0 (|K'| the value) flags a record that needs
 //                               the near-plane segment factor.  Epanechnikov
 //                               kernel: K' = (4/3) kappa log2 e, se = mz^2
-//   g5 = (r, g, b, mz)          colour after the activation (0 in X-ray mode)
+//   g5 = (r, g, b, mz)          colour after the activation
 //   g6 = (cx, cy, a, P)         tile-culling ellipse (see cull_row in the
 //   g7 = (R, ymax, yl, on)        preprocess source); on = 0: no culling
+// X-ray mode: g0, g6, g7 as above, the ray frame's fields g1 = (r00, r01, r11, 0),
+// g2 = (s0, s1, K'/|v0|, se |v0|^2) (raster_xray.hip), and for what needs the L-frame
+// g3 = (A00, A10, A20, A01), g4 = (A11, A21, v0x, v0y), g5 = (v0z, K', se, mz).
 // With the splatting model (VGR_ALPHA_SPLAT) g0, g1, g5, g6, g7 keep their
 // meaning (l = 0) and g2 = (Q11, 0, 0, 0), g3 = (c00, c01, c11, 0),
 // g4 = (0, 0, o, 0) with c = log2(e) (C00/2, C01, C11/2), C = Sigma'^-1:
@@ -152,9 +155,9 @@ struct Buffers {
     int32_t *last_id;    // total pixels: Gaussian index of last blended (-1)
     float4 *rgrad;       // n_views * n * 4 float4 (record gradients)
     uint64_t *pmask;     // pmask_words(): bound pre-test lane masks of each B-record
-                         // batch of a tile list, written by the forward where
-                         // raster_keeps_masks() and read by the backward (with
-                         // the per-pixel window: the pairs composited)
+                         // batch of a tile list, written by the forward and read
+                         // by the backward with the splatting opacity (with the
+                         // per-pixel window: the pairs composited)
     // colour with the volumetric opacity (raster_quads()): what the backward needs
     // of the forward's decisions, per 4x4 pixel block q of a tile (region by region,
     // four blocks per 8x8 region) and batch of 64 list entries, bq = quad_batch() *
@@ -185,17 +188,11 @@ struct Buffers {
     const ViewInfo *views;
 };
 
-// The forward keeps, for each B-record batch of a tile's list, every lane's
-// bound pre-test mask per pixel slot (bit q: record q of the batch may reach
-// the pixel), where it computes them for the whole batch: colour mode, and
-// X-ray mode with one pixel per lane.  Batch k of tile t (records
-// start_t + B k ...) keeps its masks at words
+// The forward walk of raster.hip keeps, for each B-record batch of a tile's list, every
+// lane's bound pre-test mask per pixel slot (bit q: record q of the batch may reach the
+// pixel).  Batch k of tile t (records start_t + B k ...) keeps its masks at words
 // (((start_t + B k) 64/B + 64 t + lane) * ppl + slot): tile t's batches span
 // fewer than len_t 64/B + 64 slots, so the tiles' spans do not overlap.
-inline bool raster_keeps_masks(int mode, int tile_w, int tile_h)
-{
-    return mode == VGR_MODE_COLOR || tile_w * tile_h == 64;
-}
 inline int64_t pmask_words(int64_t instances, int32_t total_tiles, int tile_w, int tile_h,
                            int batch)
 {
@@ -208,6 +205,11 @@ inline bool raster_quads(const RenderParams &rp)
 {
     return rp.mode == VGR_MODE_COLOR && rp.alpha_model == VGR_ALPHA_VOLUMETRIC &&
            rp.pixel_window == 0;
+}
+// Calls of raster_xray.hip.
+__host__ __device__ inline bool raster_xray(const RenderParams &rp)
+{
+    return rp.mode == VGR_MODE_XRAY && rp.alpha_model == VGR_ALPHA_VOLUMETRIC;
 }
 __host__ __device__ inline int quad_blocks(int tile_w, int tile_h)
 {
@@ -294,6 +296,7 @@ hipError_t launch_raster_bwd(const RenderParams &rp, const Buffers &b, bool coun
 int64_t raster_workgroups(const RenderParams &rp);
 // Forward and backward of colour with the volumetric opacity, and their workgroups.
 int64_t color_workgroups(const RenderParams &rp);
+hipError_t launch_xray(const RenderParams &rp, const Buffers &b, bool fwd, bool count, hipStream_t s);
 hipError_t launch_color_fwd(const RenderParams &rp, const Buffers &b, bool count, hipStream_t s);
 hipError_t launch_color_bwd(const RenderParams &rp, const Buffers &b, bool count, hipStream_t s);
 // Per-pixel window: bytes of the pair buffers per instance of capacity.
