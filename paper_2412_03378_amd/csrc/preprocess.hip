@@ -463,16 +463,20 @@ __device__ inline float d2max_of(bool epan, float r)
     return epan ? 1.0f - powf(r, -2.0f / 3.0f) : 2.0f * logf(r);
 }
 
+// (Three waves per SIMD: the many-view form with 16 SH coefficients is at the edge, and
+// one wave fewer took 3.10 instead of 2.68 ms on 16 views of 3M Gaussians.)
 template <int DEG, bool MULTI, bool SPLAT>
-__global__ __launch_bounds__(256) void preprocess_kernel(RenderParams rp, Buffers b,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void preprocess_kernel(RenderParams rp, Buffers b,
                                                          const float *__restrict__ means,
                                                          const float *__restrict__ quats,
                                                          const float *__restrict__ scales,
                                                          const float *__restrict__ dens,
-                                                         const float *__restrict__ sh)
+                                                         const float *__restrict__ sh, int chunk)
 {
     // One thread per Gaussian for all views of the call: its parameters (and
     // its SH row, from the first view that sees it) are read from HBM once.
+    // (A grid with too few blocks for the chip splits the views over blockIdx.y, in
+    // chunks of `chunk` views: view_chunk.)
     // MULTI = false is the one-view form: no loop, and the SH row is not kept
     // across iterations (fewer registers, higher occupancy).  SPLAT: the record
     // of the 3DGS splatting model (the density input is the peak opacity).
@@ -490,10 +494,11 @@ __global__ __launch_bounds__(256) void preprocess_kernel(RenderParams rp, Buffer
 
     // per view, this block's items with instances (wave ballots, added in LDS)
     __shared__ uint32_t s_vis[kMaxViews];
-    const int n_views = MULTI ? rp.n_views : 1;
-    for (int v = (int)threadIdx.x; v < n_views; v += (int)blockDim.x) s_vis[v] = 0u;
+    const int first = MULTI ? (int)blockIdx.y * chunk : 0;
+    const int last = MULTI ? min(first + chunk, rp.n_views) : 1;
+    for (int v = first + (int)threadIdx.x; v < last; v += (int)blockDim.x) s_vis[v] = 0u;
     __syncthreads();
-    for (int v = 0; v < n_views; ++v) {
+    for (int v = first; v < last; ++v) {
         const ViewInfo &vi = b.views[v];
         const int64_t item = (int64_t)v * rp.n + i;
         uint32_t key = 0xFFFFFFFFu, count = 0;
@@ -677,10 +682,11 @@ __global__ __launch_bounds__(256) void preprocess_kernel(RenderParams rp, Buffer
     if ((threadIdx.x & 63) == 0) s_wsum[threadIdx.x >> 6] = wsum;
     __syncthreads();
     if (threadIdx.x == 0)
-        b.blk_counts[blockIdx.x] = s_wsum[0] + s_wsum[1] + s_wsum[2] + s_wsum[3];
+        b.blk_counts[(size_t)gridDim.x * (rp.n_views + blockIdx.y) + blockIdx.x] =
+            s_wsum[0] + s_wsum[1] + s_wsum[2] + s_wsum[3];
     // items with instances per (view, block), in item order (view-major)
-    for (int v = (int)threadIdx.x; v < n_views; v += (int)blockDim.x)
-        b.blk_counts[gridDim.x + (size_t)v * gridDim.x + blockIdx.x] = s_vis[v];
+    for (int v = first + (int)threadIdx.x; v < last; v += (int)blockDim.x)
+        b.blk_counts[(size_t)v * gridDim.x + blockIdx.x] = s_vis[v];
 }
 
 // Exclusive scan over the 256 threads of a block; *total gets the sum.
@@ -708,8 +714,8 @@ __device__ __forceinline__ uint32_t emit_block_scan(uint32_t v, uint32_t *wsum, 
 }
 
 // Block 0: instance total into d_total[4].  Block 1: exclusive scan, in
-// place, of the nc per-(view, block) counts of items with instances that
-// follow the nb instance partials, and their total (the items the depth sort
+// place, of the nc per-(view, block) counts of items with instances, which the
+// nb instance partials follow, and their total (the items the depth sort
 // takes) into d_total[6].
 __global__ __launch_bounds__(256) void count_total_kernel(uint32_t *__restrict__ parts,
                                                            int64_t nb, int64_t nc,
@@ -719,7 +725,7 @@ __global__ __launch_bounds__(256) void count_total_kernel(uint32_t *__restrict__
     __shared__ uint32_t s_part[4];
     if (blockIdx.x == 0) {
         uint32_t acc = 0;
-        for (int64_t k = threadIdx.x; k < nb; k += 256) acc += parts[k];
+        for (int64_t k = threadIdx.x; k < nb; k += 256) acc += parts[nc + k];
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
         if ((threadIdx.x & 63) == 0) s_part[threadIdx.x >> 6] = acc;
@@ -732,7 +738,7 @@ __global__ __launch_bounds__(256) void count_total_kernel(uint32_t *__restrict__
         return;
     }
     // 4096 counts per round, 16 consecutive ones per thread
-    uint32_t *c = parts + nb;
+    uint32_t *c = parts;
     uint32_t carry = 0;
     for (int64_t base = 0; base < nc; base += 4096) {   // uniform
         const int64_t k0 = base + (int64_t)threadIdx.x * 16;
@@ -773,7 +779,7 @@ __global__ __launch_bounds__(256) void compact_items_kernel(RenderParams rp, Buf
     uint32_t tot;
     const uint32_t r = emit_block_scan(vis ? 1u : 0u, s_w, &tot);
     if (vis) {
-        const uint32_t pos = b.blk_counts[nb + c] + r;
+        const uint32_t pos = b.blk_counts[c] + r;
         b.depth_key[pos] = key;
         b.item_ids[pos] = (uint32_t)item;
     }
@@ -1508,14 +1514,28 @@ hipError_t launch_fill_f32(float *p, float v, int64_t n, hipStream_t s)
     return hipGetLastError();
 }
 
+// Views per block of the preprocess: all of them (a Gaussian's parameters and SH row
+// are read once) unless the Gaussians alone leave the chip idle, then as many chunks
+// of views as bring kPreBlocks blocks: a view takes a thread about 6 us of dependent
+// arithmetic.  All views per block and chunks: X-ray, 12 views of 8k Gaussians 98 and
+// 33 us, 8 views of 60k 86 and 60 us (512 blocks: 58, 1024: 66, 4096: 63).
+constexpr int64_t kPreBlocks = 2048;
+int view_chunk(const RenderParams &rp)
+{
+    const int64_t blocks = grid_for(rp.n, 256);
+    const int64_t chunks = blocks >= kPreBlocks ? 1 : (kPreBlocks + blocks - 1) / (blocks > 0 ? blocks : 1);
+    return chunks >= rp.n_views ? 1 : (int)((rp.n_views + chunks - 1) / chunks);
+}
+
 hipError_t launch_preprocess(const RenderParams &rp, const Buffers &b, const float *means,
                              const float *quats, const float *scales, const float *dens,
                              const float *sh, hipStream_t s)
 {
-    const unsigned grid = grid_for(rp.n, 256);
+    const int chunk = view_chunk(rp);
+    const dim3 grid(grid_for(rp.n, 256), (unsigned)((rp.n_views + chunk - 1) / chunk));
     const int deg = rp.mode == VGR_MODE_COLOR ? rp.sh_degree : 0;
     const bool multi = rp.n_views > 1, splat = rp.alpha_model == VGR_ALPHA_SPLAT;
-#define VGR_PRE(D, M, S) preprocess_kernel<D, M, S><<<grid, 256, 0, s>>>(rp, b, means, quats, scales, dens, sh)
+#define VGR_PRE(D, M, S) preprocess_kernel<D, M, S><<<grid, 256, 0, s>>>(rp, b, means, quats, scales, dens, sh, chunk)
 #define VGR_PRE_DEG(M, S)            \
     switch (deg) {                   \
     case 0: VGR_PRE(0, M, S); break; \
@@ -1532,8 +1552,8 @@ hipError_t launch_preprocess(const RenderParams &rp, const Buffers &b, const flo
 #undef VGR_PRE
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    count_total_kernel<<<2, 256, 0, s>>>(b.blk_counts, (int64_t)grid,
-                                         (int64_t)grid * rp.n_views, b.d_total, b.h_total);
+    count_total_kernel<<<2, 256, 0, s>>>(b.blk_counts, (int64_t)grid.x * grid.y,
+                                         (int64_t)grid.x * rp.n_views, b.d_total, b.h_total);
     return hipGetLastError();
 }
 
@@ -1548,9 +1568,9 @@ hipError_t launch_compact_items(const RenderParams &rp, const Buffers &b, hipStr
 
 int64_t preprocess_blocks(int64_t n, int32_t n_views)
 {
-    // instance partial sums, then the per-(view, block) counts of items with
-    // instances (one thread per Gaussian covers all views)
-    return (1 + (int64_t)n_views) * (int64_t)grid_for(n, 256);
+    // per-(view, block) counts of items with instances, then instance partial
+    // sums (one per view at most: view_chunk)
+    return 2 * (int64_t)n_views * (int64_t)grid_for(n, 256);
 }
 
 hipError_t launch_gather_counts(const Buffers &b, int64_t m, int32_t total_tiles,

@@ -175,7 +175,7 @@ struct Buffers {
                          // replay for composited pairs: (dL/dy, 0 where alpha was
                          // clamped; alpha T_before)
     int32_t *wcount;     // total pixels: pairs composited
-    uint32_t *blk_counts;// preprocess blocks: instances per block
+    uint32_t *blk_counts;// preprocess blocks: items with instances per (view, block),
     uint32_t *d_total;   // [0] = instance count K, [1] overflow flag, [4] K from the
                          // preprocess, [6] items with instances (the first of the
                          // depth order), [3] long tiles (the first of tile_order)
@@ -260,8 +260,8 @@ hipError_t launch_fill_f32(float *p, float v, int64_t n, hipStream_t s);
 hipError_t launch_preprocess(const RenderParams &rp, const Buffers &b, const float *means,
                              const float *quats, const float *scales, const float *dens,
                              const float *sh, hipStream_t s);
-// Size of Buffers::blk_counts: the instance partial sums per preprocess block,
-// then the counts of items with instances per (view, block).
+// Size of Buffers::blk_counts: the counts of items with instances per (view, block),
+// then the instance partial sums.
 int64_t preprocess_blocks(int64_t n, int32_t n_views);
 // The items with instances (depth key != 0xFFFFFFFF in key2, item order) to
 // the front of (depth_key, item_ids), in item order, for the depth sort of
