@@ -821,46 +821,52 @@ __global__ __launch_bounds__(kGatherThreads) void gather_counts_kernel(
     }
 }
 
-// Emission of the (tile, Gaussian) pairs in depth order.  Each 256-thread
-// block owns 64 consecutive depth-sorted Gaussians, whose instance ranges are
-// contiguous.  Their candidate tile rows (the rows of each rectangle, in
-// Gaussian then row order) are processed 1024 at a time, four consecutive
-// rows per thread: each thread finds the owning Gaussian by binary search
-// over the 64 row prefixes and culls its rows to tile intervals (the same
-// intervals the preprocess counted); a block scan of the interval lengths
-// gives each row its first instance; then each thread writes instances
-// e, e + 256, ..., finding the row of instance e by binary search over the
-// row starts.
-constexpr int kEmitRows = 1024;
-constexpr int kEmitThreads = 256;
-constexpr int kEmitRowsPerThread = kEmitRows / kEmitThreads;
+// Emission of the (tile, Gaussian) pairs in the items' order.  Each wave owns
+// 2^lg consecutive items, whose instance ranges are contiguous.  Their candidate
+// tile rows (the rows of each rectangle, in item then row order) are processed
+// 256 at a time, four consecutive rows per lane: each lane finds the owning item
+// by binary search over the row prefixes and culls its rows to tile intervals (the
+// same intervals the preprocess counted); a scan of the interval lengths gives each
+// row its first instance.  The rows' lanes then write their tiles into LDS,
+// kEmitWindow instances at a time, from where they leave in order.
+//
+// The kernel waits for a chain of loads per item (offset, item, its record) and
+// little else, so what counts is items in flight: a wave of its own per 64 items has
+// four times as many as 256 threads per 64 items did (168 -> 113 us for 1.5M items,
+// 15.8M instances; windows of 256 and 1024 the same; writing through a search of the
+// rows for every instance instead of the window, 3 % slower).
+constexpr int kEmitThreads = 64;
+constexpr int kEmitRowsPerThread = 4;
+constexpr int kEmitRows = kEmitThreads * kEmitRowsPerThread;
+constexpr uint32_t kEmitWindow = 512;
+// (12 views of 8k Gaussians, scan and emission: 35 us at 256 to 2048 waves, 39 at 4096,
+// 59 at 16384)
+constexpr int64_t kEmitWaves = 1024;
 
 __global__ __launch_bounds__(kEmitThreads) void emit_kernel(RenderParams rp, Buffers b, int64_t m,
-                                                  int64_t capacity)
+                                                            int64_t capacity, int lg)
 {
     __shared__ uint32_t s_item[64];
     __shared__ ushort4 s_rect[64];
     __shared__ CullRows s_cull[64];
     __shared__ int32_t s_toff[64], s_tx[64];
     __shared__ uint32_t s_rowbeg[65];              // first candidate row of each Gaussian
-    __shared__ uint32_t s_rstart[kEmitRows + 1];   // first instance of each row of the chunk
-    __shared__ uint32_t s_rtile[kEmitRows];        // tile row << 16 | first tile column
-    __shared__ uint8_t s_rg[kEmitRows];            // owning Gaussian (0..63)
-    __shared__ uint32_t s_wsum[kEmitThreads / 64];
+    __shared__ uint32_t s_tile[kEmitWindow];       // instances of the window: tile,
+    __shared__ uint8_t s_own[kEmitWindow];         // owning Gaussian (0..63)
     __shared__ uint32_t s_gemit[64];               // instances found per Gaussian
     const int tid = threadIdx.x;
-    const int64_t j0 = (int64_t)blockIdx.x * 64;
+    const int items = 1 << lg;
+    const int64_t j0 = (int64_t)blockIdx.x << lg;
     // items past those with instances (they sort last) emit nothing (uniform)
     if (j0 >= (int64_t)b.d_total[6]) return;
-    const int64_t jend = min(j0 + 64, m);
     const uint32_t base = b.offsets[j0];
-    if (tid < 64) {   // wave 0: the block's Gaussians and their candidate row counts
+    {   // the wave's Gaussians and their candidate row counts
         const int64_t j = j0 + tid;
         CullRows cr = { 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f };
         ushort4 rect = make_ushort4(0, 0, 0, 0);
         uint32_t item = 0, rows = 0;
         int32_t toff = 0, txs = 0;
-        if (j < m && b.offsets[j + 1] > b.offsets[j]) {   // a Gaussian with instances
+        if (tid < items && j < m && b.offsets[j + 1] > b.offsets[j]) {   // with instances
             item = b.item_ids[j];
             rect = b.rect[item];
             const float4 c6 = b.geom[(size_t)item * kRecVec + 6];
@@ -891,17 +897,19 @@ __global__ __launch_bounds__(kEmitThreads) void emit_kernel(RenderParams rp, Buf
     uint32_t done = 0;   // instances of the earlier chunks
     for (uint32_t c0 = 0; c0 < nrows; c0 += kEmitRows) {
         const uint32_t cn = min((uint32_t)kEmitRows, nrows - c0);
-        uint32_t cnt[kEmitRowsPerThread];
+        uint32_t cnt[kEmitRowsPerThread], tile[kEmitRowsPerThread];
+        int own[kEmitRowsPerThread];
         uint32_t sum = 0;
 #pragma unroll
         for (int i = 0; i < kEmitRowsPerThread; ++i) {
             const uint32_t rl = (uint32_t)(tid * kEmitRowsPerThread + i);
-            cnt[i] = 0;
+            cnt[i] = tile[i] = 0;
+            own[i] = 0;
             if (rl < cn) {
                 const uint32_t r = c0 + rl;
                 // largest g with s_rowbeg[g] <= r: Gaussians without rows share
                 // their prefix with the next one, which the search prefers
-                int lo = 0, hi = 63;
+                int lo = 0, hi = items - 1;
                 while (lo < hi) {
                     const int mid = (lo + hi + 1) >> 1;
                     if (s_rowbeg[mid] <= r) lo = mid;
@@ -910,57 +918,53 @@ __global__ __launch_bounds__(kEmitThreads) void emit_kernel(RenderParams rp, Buf
                 const ushort4 rect = s_rect[lo];
                 const int row = (int)rect.y + (int)(r - s_rowbeg[lo]);
                 int t0 = 0, t1 = -1;
-                if (cull_row(s_cull[lo], row, rp.tile_w, rp.tile_h, rect.x, rect.z, t0, t1))
+                if (cull_row(s_cull[lo], row, rp.tile_w, rp.tile_h, rect.x, rect.z, t0, t1)) {
                     cnt[i] = (uint32_t)(t1 - t0 + 1);
-                if (cnt[i]) atomicAdd(&s_gemit[lo], cnt[i]);
-                s_rtile[rl] = ((uint32_t)row << 16) | (uint32_t)(t0 & 0xFFFF);
-                s_rg[rl] = (uint8_t)lo;
+                    atomicAdd(&s_gemit[lo], cnt[i]);
+                }
+                tile[i] = (uint32_t)(s_toff[lo] + row * s_tx[lo] + t0);
+                own[i] = lo;
             }
             sum += cnt[i];
         }
-        uint32_t chunk;
-        uint32_t run = done + emit_block_scan(sum, s_wsum, &chunk);
+        uint32_t inc = sum;
 #pragma unroll
-        for (int i = 0; i < kEmitRowsPerThread; ++i) {
-            const uint32_t rl = (uint32_t)(tid * kEmitRowsPerThread + i);
-            if (rl < cn) s_rstart[rl] = run;
-            run += cnt[i];
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint32_t t = __shfl_up(inc, d, 64);
+            if (tid >= d) inc += t;
         }
-        if (tid == 0) s_rstart[cn] = done + chunk;
-        __syncthreads();
-        for (uint32_t e = done + (uint32_t)tid; e < done + chunk; e += kEmitThreads) {
-            // largest k with s_rstart[k] <= e (rows without instances share the
-            // start of the next row, which the search prefers)
-            int lo = 0, hi = (int)cn - 1;
-            while (lo < hi) {
-                const int mid = (lo + hi + 1) >> 1;
-                if (s_rstart[mid] <= e) lo = mid;
-                else hi = mid - 1;
+        const uint32_t run0 = done + inc - sum, chunk = __builtin_amdgcn_readlane(inc, 63);
+        for (uint32_t w0 = done; w0 < done + chunk; w0 += kEmitWindow) {   // uniform
+            const uint32_t wn = min(kEmitWindow, done + chunk - w0);
+            uint32_t run = run0;
+#pragma unroll
+            for (int i = 0; i < kEmitRowsPerThread; ++i) {
+                // instances run .. run + cnt of the row, cut to the window
+                const uint32_t e1 = min(run + cnt[i], w0 + wn);
+                for (uint32_t e = max(run, w0); e < e1; ++e) {
+                    s_tile[e - w0] = tile[i] + (e - run);
+                    s_own[e - w0] = (uint8_t)own[i];
+                }
+                run += cnt[i];
             }
-            const int g = s_rg[lo];
-            const ushort4 rr = s_rect[g];
-            // the preprocess counted exactly these tiles; the clamp only keeps
-            // a miscount (none is expected) inside the Gaussian's own rectangle
-            const int ty = min(max((int)(s_rtile[lo] >> 16), (int)rr.y), (int)rr.w);
-            const int tx = min(max((int)(s_rtile[lo] & 0xFFFFu) + (int)(e - s_rstart[lo]),
-                                   (int)rr.x), (int)rr.z);
-            const int64_t pos = (int64_t)base + e;
-            if (pos < capacity) {
-                b.inst_key[pos] = (uint32_t)(s_toff[g] + ty * s_tx[g] + tx);
-                b.inst_val[pos] = s_item[g];
+            __syncthreads();
+            for (uint32_t e = (uint32_t)tid; e < wn; e += kEmitThreads) {
+                const int64_t pos = (int64_t)base + w0 + e;
+                if (pos < capacity) {
+                    b.inst_key[pos] = s_tile[e];
+                    b.inst_val[pos] = s_item[s_own[e]];
+                }
             }
+            __syncthreads();
         }
         done += chunk;
-        __syncthreads();   // the next chunk rewrites the row tables
     }
     // every Gaussian must have produced exactly the tile count the preprocess
     // gave it (which sized the lists): count the items that did not
-    if (tid < 64) {
-        const int64_t j = j0 + tid;
-        const uint32_t want = j < m ? b.offsets[j + 1] - b.offsets[j] : 0u;
-        const uint64_t bad = __builtin_amdgcn_ballot_w64(s_gemit[tid] != want);
-        if (tid == 0 && bad != 0) atomicAdd(&b.d_total[7], (uint32_t)__builtin_popcountll(bad));
-    }
+    const int64_t j = j0 + tid;
+    const uint32_t want = tid < items && j < m ? b.offsets[j + 1] - b.offsets[j] : 0u;
+    const uint64_t bad = __builtin_amdgcn_ballot_w64(s_gemit[tid] != want);
+    if (tid == 0 && bad != 0) atomicAdd(&b.d_total[7], (uint32_t)__builtin_popcountll(bad));
 }
 
 // Per-tile [start, end) of the tile-sorted instance list.  Keys at or past
@@ -1587,7 +1591,10 @@ hipError_t launch_gather_counts(const Buffers &b, int64_t m, int32_t total_tiles
 hipError_t launch_emit(const RenderParams &rp, const Buffers &b, int64_t m, int64_t capacity,
                        hipStream_t s)
 {
-    emit_kernel<<<grid_for(m, 64), kEmitThreads, 0, s>>>(rp, b, m, capacity);   // 64 Gaussians per block
+    // 64 items per wave, fewer (down to 4) in calls with less than kEmitWaves waves
+    int lg = 6;
+    while (lg > 2 && (m >> lg) < kEmitWaves) --lg;
+    emit_kernel<<<grid_for(m, 1 << lg), kEmitThreads, 0, s>>>(rp, b, m, capacity, lg);
     return hipGetLastError();
 }
 
