@@ -693,12 +693,16 @@ int enqueue_forward(vgr_ctx *c, const Prepared &p, const float *means, const flo
         mark_end(c, ST_PREPROCESS);
         // depth order of the (view, Gaussian) items that have instances (about
         // half of them in a wide scene: the others are culled or out of view);
-        // ties keep the item order
+        // ties keep the item order.  X-ray mode sums its terms, so its items stay
+        // in item order, which also leaves the emission's reads and the tile
+        // lists' records side by side (8 views of 60k Gaussians: 63 us and 14 launches
+        // less; 64 of 500k: 1.0 ms, and 2.3 ms less in the emission and the tile sort).
         mark(c, ST_SORT_DEPTH);
         // (their number, d_total[6], comes from the preprocess's totals kernel)
         HIP_TRY(c, launch_compact_items(rp, b, s));
-        HIP_TRY(c, launch_radix_sort(b.depth_key, b.item_ids, b.key2, b.item2, b.d_total + 6, m, 32,
-                                     ptr<uint32_t>(c->sort_tmp), s));
+        if (rp.mode != VGR_MODE_XRAY)
+            HIP_TRY(c, launch_radix_sort(b.depth_key, b.item_ids, b.key2, b.item2, b.d_total + 6, m,
+                                         32, ptr<uint32_t>(c->sort_tmp), s));
         mark_end(c, ST_SORT_DEPTH);
         mark(c, ST_SCAN_EMIT);
         // eager: the items with instances come first in depth order, and their
