@@ -6,6 +6,7 @@
 
 #include <string>
 #include <map>
+#include <utility>
 #include <vector>
 
 #include "vgr_internal.h"
@@ -702,7 +703,7 @@ int enqueue_forward(vgr_ctx *c, const Prepared &p, const float *means, const flo
         HIP_TRY(c, launch_compact_items(rp, b, s));
         if (rp.mode != VGR_MODE_XRAY)
             HIP_TRY(c, launch_radix_sort(b.depth_key, b.item_ids, b.key2, b.item2, b.d_total + 6, m,
-                                         32, ptr<uint32_t>(c->sort_tmp), s));
+                                         32, ptr<uint32_t>(c->sort_tmp), false, s));
         mark_end(c, ST_SORT_DEPTH);
         mark(c, ST_SCAN_EMIT);
         // eager: the items with instances come first in depth order, and their
@@ -732,7 +733,15 @@ int enqueue_forward(vgr_ctx *c, const Prepared &p, const float *means, const flo
         HIP_TRY(c, launch_gather_counts(b, mv, rp.total_tiles, ptr<uint32_t>(c->scan_tmp), s));
         HIP_TRY(c, launch_count_scan(b.cnt_sorted, b.offsets, mv, ptr<uint32_t>(c->scan_tmp),
                                      b.d_total, K, s));
-        HIP_TRY(c, launch_emit(rp, b, mv, K, s));
+        // an odd number of tile sort passes starts from the second pair of lists, to
+        // end in the first
+        const int tile_bits = bits_for(p.tiles);
+        Buffers be = b;
+        if (radix_passes(K, tile_bits) & 1) {
+            std::swap(be.inst_key, be.inst_key2);
+            std::swap(be.inst_val, be.inst_val2);
+        }
+        HIP_TRY(c, launch_emit(rp, be, mv, K, s));
         mark_end(c, ST_SCAN_EMIT);
         mark(c, ST_SORT_TILES);
         if (rp.tile_resort) {
@@ -740,13 +749,13 @@ int enqueue_forward(vgr_ctx *c, const Prepared &p, const float *means, const flo
             // ray; the stable tile sort below keeps that order within each tile
             uint32_t *k1 = ptr<uint32_t>(c->rs_key), *i1 = ptr<uint32_t>(c->rs_idx);
             uint32_t *k2 = ptr<uint32_t>(c->rs_key2), *i2 = ptr<uint32_t>(c->rs_idx2);
-            HIP_TRY(c, launch_resort_keys(rp, b, k1, i1, K, s));
+            HIP_TRY(c, launch_resort_keys(rp, be, k1, i1, K, s));
             HIP_TRY(c, launch_radix_sort(k1, i1, k2, i2, b.d_total, K, 32,
-                                         ptr<uint32_t>(c->sort_tmp), s));
-            HIP_TRY(c, launch_resort_permute(b, i1, k2, i2, K, s));
+                                         ptr<uint32_t>(c->sort_tmp), false, s));
+            HIP_TRY(c, launch_resort_permute(be, i1, k2, i2, K, s));
         }
-        HIP_TRY(c, launch_radix_sort(b.inst_key, b.inst_val, b.inst_key2, b.inst_val2, b.d_total, K,
-                                     bits_for(p.tiles), ptr<uint32_t>(c->sort_tmp), s));
+        HIP_TRY(c, launch_radix_sort(be.inst_key, be.inst_val, be.inst_key2, be.inst_val2, b.d_total,
+                                     K, tile_bits, ptr<uint32_t>(c->sort_tmp), true, s));
         mark_end(c, ST_SORT_TILES);
     } else {
         HIP_TRY(c, launch_fill_u32(b.d_total, 0u, 2, s));
@@ -989,7 +998,7 @@ int vgr_sort_pairs(vgr_ctx *c, uint32_t *keys, uint32_t *vals, int64_t n, int32_
     uint32_t *dn = ptr<uint32_t>(c->words) + 2;
     HIP_TRY(c, launch_fill_u32(dn, (uint32_t)n, 1, s));
     HIP_TRY(c, launch_radix_sort(keys, vals, ptr<uint32_t>(c->inst_key2), ptr<uint32_t>(c->inst_val2),
-                                 dn, n, bits, ptr<uint32_t>(c->sort_tmp), s));
+                                 dn, n, bits, ptr<uint32_t>(c->sort_tmp), false, s));
     return VGR_OK;
 }
 
@@ -1015,7 +1024,7 @@ int vgr_sort_pairs_static(vgr_ctx *c, uint32_t *keys, uint32_t *vals, int64_t n,
     uint32_t *dn = tmp + kStaticRadixWords;
     hipStream_t s = c->stream;
     HIP_TRY(c, launch_fill_u32(dn, (uint32_t)n, 1, s));
-    HIP_TRY(c, launch_radix_sort(keys, vals, k2, v2, dn, n, bits, tmp, s));
+    HIP_TRY(c, launch_radix_sort(keys, vals, k2, v2, dn, n, bits, tmp, false, s));
     return VGR_OK;
 }
 

@@ -332,9 +332,15 @@ int64_t radix_tmp_words(int64_t n_bound)
     return 256 * (nb_own > nb_small ? nb_own : nb_small) + 256;
 }
 
+int radix_passes(int64_t n_bound, int bits)
+{
+    (void)n_bound;
+    return (bits + 7) / 8;
+}
+
 hipError_t launch_radix_sort(uint32_t *keys, uint32_t *vals, uint32_t *keys2, uint32_t *vals2,
                              const uint32_t *d_n, int64_t n_bound, int bits, uint32_t *tmp,
-                             hipStream_t s)
+                             bool stay, hipStream_t s)
 {
     if (n_bound <= 0 || bits <= 0) return hipSuccess;
     const bool small = n_bound <= kSmallSort;
@@ -342,7 +348,7 @@ hipError_t launch_radix_sort(uint32_t *keys, uint32_t *vals, uint32_t *keys2, ui
     const int64_t table = 256 * nb;
     uint32_t *hist = tmp;            // digit-major per-block counts, then their row scans
     uint32_t *tot = tmp + table;     // per-digit totals
-    const int passes = (bits + 7) / 8;
+    const int passes = radix_passes(n_bound, bits);
     // spread the bits evenly over the passes (each at most 8)
     int shift = 0;
     uint32_t *ki = keys, *vi = vals, *ko = keys2, *vo = vals2;
@@ -364,7 +370,7 @@ hipError_t launch_radix_sort(uint32_t *keys, uint32_t *vals, uint32_t *keys2, ui
         tt = ki; ki = ko; ko = tt;
         tt = vi; vi = vo; vo = tt;
     }
-    if (ki != keys) {
+    if (ki != keys && !stay) {
         const int64_t grid = (n_bound + 255) / 256 < 65536 ? (n_bound + 255) / 256 : 65536;
         copy_pairs_kernel<<<dim3((unsigned)grid), 256, 0, s>>>(ki, vi, keys, vals, d_n, n_bound);
     }

@@ -328,10 +328,12 @@ hipError_t launch_count_scan(const uint32_t *in, uint32_t *out, int64_t n, uint3
 
 // Radix sort of (key, val) u32 pairs; element count read from *d_n on the
 // device, grids sized for n_bound.  Ping-pong buffers keys/vals <-> keys2/vals2;
-// the sorted result ends in (keys, vals).  tmp: radix_tmp_words(n_bound).
+// the sorted result ends in (keys, vals), or with stay after an odd number of passes
+// where the last one left it, (keys2, vals2).  tmp: radix_tmp_words(n_bound).
+int radix_passes(int64_t n_bound, int bits);
 int64_t radix_tmp_words(int64_t n_bound);
 hipError_t launch_radix_sort(uint32_t *keys, uint32_t *vals, uint32_t *keys2, uint32_t *vals2,
                              const uint32_t *d_n, int64_t n_bound, int bits, uint32_t *tmp,
-                             hipStream_t s);
+                             bool stay, hipStream_t s);
 
 }  // namespace vgr
