@@ -969,17 +969,31 @@ __global__ __launch_bounds__(kEmitThreads) void emit_kernel(RenderParams rp, Buf
 
 // Per-tile [start, end) of the tile-sorted instance list.  Keys at or past
 // n_tiles (none are emitted; the check keeps a bad key from writing outside
-// the ranges array) are ignored.
+// the ranges array) are ignored.  Four keys a thread, one load (15.8M keys: 33 -> 16
+// us).
 __global__ void ranges_kernel(const uint32_t *__restrict__ keys, const uint32_t *__restrict__ d_total,
                               uint2 *__restrict__ ranges, int64_t bound, uint32_t n_tiles)
 {
-    const int64_t K = d_total[0];
-    for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < K && j < bound;
-         j += (int64_t)gridDim.x * blockDim.x) {
-        const uint32_t k = keys[j];
-        if (k >= n_tiles) continue;
-        if (j == 0 || keys[j - 1] != k) ranges[k].x = (uint32_t)j;
-        if (j == K - 1 || keys[j + 1] != k) ranges[k].y = (uint32_t)(j + 1);
+    const int64_t K = min((int64_t)d_total[0], bound);
+    for (int64_t j = 4 * ((int64_t)blockIdx.x * blockDim.x + threadIdx.x); j < K;
+         j += 4 * (int64_t)gridDim.x * blockDim.x) {
+        // k[1..4], with their neighbours (past the list's ends no key)
+        uint32_t k[6];
+        k[0] = j > 0 ? keys[j - 1] : ~0u;
+        if (j + 3 < K) {
+            const uint4 v = *reinterpret_cast<const uint4 *>(keys + j);
+            k[1] = v.x; k[2] = v.y; k[3] = v.z; k[4] = v.w;
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) k[1 + i] = j + i < K ? keys[j + i] : ~0u;
+        }
+        k[5] = j + 4 < K ? keys[j + 4] : ~0u;
+#pragma unroll
+        for (int i = 1; i < 5; ++i) {
+            if (k[i] >= n_tiles) continue;
+            if (k[i - 1] != k[i]) ranges[k[i]].x = (uint32_t)(j + i - 1);
+            if (k[i + 1] != k[i]) ranges[k[i]].y = (uint32_t)(j + i);
+        }
     }
 }
 
@@ -1607,7 +1621,7 @@ hipError_t launch_ranges(const Buffers &b, int64_t bound, int32_t total_tiles, b
         if (e != hipSuccess) return e;
     }
     if (bound <= 0) return hipSuccess;
-    unsigned g = grid_for(bound, 256);
+    unsigned g = grid_for(bound, 1024);   // four keys a thread
     if (g > 16384) g = 16384;
     ranges_kernel<<<g, 256, 0, s>>>(b.inst_key, b.d_total, b.ranges, bound, (uint32_t)total_tiles);
     return hipGetLastError();
