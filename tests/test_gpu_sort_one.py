@@ -32,3 +32,25 @@ def test_sort_one_workgroup(n, bits, kind):
     order = np.argsort(k, kind="stable")
     assert np.array_equal(kt.cpu().numpy().view(np.uint32), k[order])
     assert np.array_equal(vt.cpu().numpy().view(np.uint32), v[order])
+
+
+@pytest.mark.parametrize("skip", [0, 1, 3])
+@pytest.mark.parametrize("n", [10241, 4194304 + 4099])
+def test_sort_unaligned_keys(n, skip):
+    """Tables of counts from keys that do and do not start at 16 bytes, in both tile
+    sizes, with a last tile that is not whole."""
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    from paper_2412_03378_amd import Renderer
+    R, dev = Renderer(0), torch.device("cuda", 0)
+    rng = np.random.default_rng(n + skip)
+    k = rng.integers(0, 1 << 20, n, dtype=np.uint64).astype(np.int32)
+    buf = torch.zeros(n + skip, dtype=torch.int32, device=dev)
+    kt = buf[skip:]
+    kt.copy_(torch.from_numpy(k))
+    vt = torch.arange(n, dtype=torch.int32, device=dev)
+    R.sort_pairs(kt, vt, 20)
+    torch.cuda.synchronize()
+    order = np.argsort(k, kind="stable")
+    assert np.array_equal(kt.cpu().numpy(), k[order])
+    assert np.array_equal(vt.cpu().numpy(), order.astype(np.int32))
