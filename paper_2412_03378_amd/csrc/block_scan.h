@@ -1,0 +1,79 @@
+// Exclusive scan of an array by one workgroup.
+#pragma once
+
+#include "vgr_internal.h"
+
+namespace vgr {
+
+namespace {
+
+constexpr int kScanThreads = 1024;
+
+// Exclusive scan, in place, of c[0..n) (16-byte aligned) by the kScanThreads threads of
+// the block; returns the total.  A serial chain of rounds, so a round takes 16384
+// words, four loads of four consecutive words a thread, all coalesced and in flight
+// before the round's one scan.
+__device__ __forceinline__ uint32_t scan_in_place(uint32_t *__restrict__ c, int64_t n)
+{
+    constexpr int W = kScanThreads / 64, Q = 4;
+    __shared__ uint32_t wsum[Q][W];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    uint32_t carry = 0;
+    for (int64_t base = 0; base < n; base += Q * 4 * kScanThreads) {   // uniform
+        uint4 v[Q];
+        uint32_t inc[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int64_t k = base + 4 * ((int64_t)q * kScanThreads + threadIdx.x);
+            if (k + 3 < n) {
+                v[q] = *reinterpret_cast<const uint4 *>(c + k);
+            } else {
+                v[q].x = k < n ? c[k] : 0u;
+                v[q].y = k + 1 < n ? c[k + 1] : 0u;
+                v[q].z = k + 2 < n ? c[k + 2] : 0u;
+                v[q].w = 0u;
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            inc[q] = v[q].x + v[q].y + v[q].z + v[q].w;
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                const uint32_t t = __shfl_up(inc[q], d, 64);
+                if (lane >= d) inc[q] += t;
+            }
+            if (lane == 63) wsum[q][w] = inc[q];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            uint32_t off = carry;
+#pragma unroll
+            for (int i = 0; i < W; ++i) {
+                const uint32_t s = wsum[q][i];
+                off += i < w ? s : 0u;
+                carry += s;
+            }
+            const int64_t k = base + 4 * ((int64_t)q * kScanThreads + threadIdx.x);
+            const uint32_t sum = v[q].x + v[q].y + v[q].z + v[q].w;
+            uint4 o;
+            o.x = off + inc[q] - sum;
+            o.y = o.x + v[q].x;
+            o.z = o.y + v[q].y;
+            o.w = o.z + v[q].z;
+            if (k + 3 < n) {
+                *reinterpret_cast<uint4 *>(c + k) = o;
+            } else {
+                if (k < n) c[k] = o.x;
+                if (k + 1 < n) c[k + 1] = o.y;
+                if (k + 2 < n) c[k + 2] = o.z;
+            }
+        }
+        __syncthreads();   // the next round rewrites wsum
+    }
+    return carry;
+}
+
+}  // namespace
+
+}  // namespace vgr
