@@ -9,22 +9,23 @@ namespace {
 
 constexpr int kScanThreads = 1024;
 
-// Exclusive scan, in place, of c[0..n) (16-byte aligned) by the kScanThreads threads of
-// the block; returns the total.  A serial chain of rounds, so a round takes 16384
-// words, four loads of four consecutive words a thread, all coalesced and in flight
-// before the round's one scan.
+// Exclusive scan, in place, of c[0..n) (16-byte aligned) by the T threads of the block;
+// returns the total.  A serial chain of rounds, so a round takes 16 T words, four loads
+// of four consecutive words a thread, all coalesced and in flight before the round's
+// one scan.
+template <int T = kScanThreads>
 __device__ __forceinline__ uint32_t scan_in_place(uint32_t *__restrict__ c, int64_t n)
 {
-    constexpr int W = kScanThreads / 64, Q = 4;
+    constexpr int W = T / 64, Q = 4;
     __shared__ uint32_t wsum[Q][W];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     uint32_t carry = 0;
-    for (int64_t base = 0; base < n; base += Q * 4 * kScanThreads) {   // uniform
+    for (int64_t base = 0; base < n; base += Q * 4 * T) {   // uniform
         uint4 v[Q];
         uint32_t inc[Q];
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
-            const int64_t k = base + 4 * ((int64_t)q * kScanThreads + threadIdx.x);
+            const int64_t k = base + 4 * ((int64_t)q * T + threadIdx.x);
             if (k + 3 < n) {
                 v[q] = *reinterpret_cast<const uint4 *>(c + k);
             } else {
@@ -54,7 +55,7 @@ __device__ __forceinline__ uint32_t scan_in_place(uint32_t *__restrict__ c, int6
                 off += i < w ? s : 0u;
                 carry += s;
             }
-            const int64_t k = base + 4 * ((int64_t)q * kScanThreads + threadIdx.x);
+            const int64_t k = base + 4 * ((int64_t)q * T + threadIdx.x);
             const uint32_t sum = v[q].x + v[q].y + v[q].z + v[q].w;
             uint4 o;
             o.x = off + inc[q] - sum;

