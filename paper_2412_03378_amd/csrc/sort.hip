@@ -409,9 +409,14 @@ hipError_t launch_count_scan(const uint32_t *in, uint32_t *out, int64_t n, uint3
     return hipGetLastError();
 }
 
-// Keys per thread of a radix pass: 4 (1024-key tiles) below 4M keys, so that
-// smaller sorts still spread over all CUs, else 16 (4096-key tiles).
-constexpr int64_t kSmallSort = 1 << 22;
+// Keys per thread of a radix pass: 4 (1024-key tiles) up to 1M keys, so that small sorts
+// still spread over all CUs, 8 up to 8M, then 16: a digit's run of a tile leaves as one
+// piece, 16 bytes of a 1024-key tile on average.
+// Depth sort and compaction at 4 and 8: 3M items (1.5M of them with instances) 177 and
+// 143 us, 1.5M a call of two views 149 and 130; 0.8M instances 146 and 153 (too few
+// blocks).  Tile sort of 4.9M instances at 8 and 16: 100 and 104 us.
+constexpr int64_t kSmallSort = 1 << 20, kMediumSort = 1 << 23;
+inline int keys_per_thread(int64_t n) { return n <= kSmallSort ? 4 : (n <= kMediumSort ? 8 : kItems); }
 
 // Words between two digits' rows of the table: rows start at 16 bytes.
 inline int64_t row_stride(int64_t nb) { return (nb + 3) & ~(int64_t)3; }
@@ -423,9 +428,13 @@ inline int64_t radix_blocks(int64_t n, int ipt) { return (n + kThreads * ipt - 1
 int64_t radix_tmp_words(int64_t n_bound)
 {
     const int64_t n = n_bound > 0 ? n_bound : 1;
-    const int64_t nb_own = radix_blocks(n, n <= kSmallSort ? 4 : kItems);
-    const int64_t nb_small = radix_blocks(n < kSmallSort ? n : kSmallSort, 4);
-    return 256 * row_stride(nb_own > nb_small ? nb_own : nb_small) + 256;
+    int64_t nb = radix_blocks(n, keys_per_thread(n));
+    for (int64_t top : { kSmallSort, kMediumSort }) {
+        const int64_t m = n < top ? n : top;
+        const int64_t k = radix_blocks(m, keys_per_thread(m));
+        nb = k > nb ? k : nb;
+    }
+    return 256 * row_stride(nb) + 256;
 }
 
 int radix_passes(int64_t n_bound, int bits)
@@ -442,8 +451,8 @@ hipError_t launch_radix_sort(uint32_t *keys, uint32_t *vals, uint32_t *keys2, ui
         radix_one_kernel<<<1, kOneThreads, 0, s>>>(keys, vals, d_n, bits, (bits + 7) / 8);
         return hipGetLastError();
     }
-    const bool small = n_bound <= kSmallSort;
-    const int64_t nb = radix_blocks(n_bound, small ? 4 : kItems);
+    const int ipt = keys_per_thread(n_bound);
+    const int64_t nb = radix_blocks(n_bound, ipt);
     const int64_t table = 256 * row_stride(nb);
     uint32_t *hist = tmp;            // digit-major per-block counts, then their row scans
     uint32_t *tot = tmp + table;     // per-digit totals
@@ -456,15 +465,11 @@ hipError_t launch_radix_sort(uint32_t *keys, uint32_t *vals, uint32_t *keys2, ui
         const uint32_t mask = (1u << dbits) - 1u;
         const dim3 g((unsigned)nb), t(kThreads);
         const int stride = (int)row_stride(nb);
-        if (small) radix_hist_kernel<4><<<g, t, 0, s>>>(ki, d_n, shift, mask, hist, stride);
-        else radix_hist_kernel<kItems><<<g, t, 0, s>>>(ki, d_n, shift, mask, hist, stride);
+#define VGR_IPT(K) (ipt == 4 ? K<4> : (ipt == 8 ? K<8> : K<kItems>))
+        VGR_IPT(radix_hist_kernel)<<<g, t, 0, s>>>(ki, d_n, shift, mask, hist, stride);
         radix_rowscan_kernel<<<256, kThreads, 0, s>>>(hist, (int)nb, stride, tot);
-        if (small)
-            radix_scatter_kernel<4><<<g, t, 0, s>>>(ki, vi, ko, vo, d_n, shift, dbits, hist, tot,
-                                                     stride);
-        else
-            radix_scatter_kernel<kItems><<<g, t, 0, s>>>(ki, vi, ko, vo, d_n, shift, dbits, hist,
-                                                          tot, stride);
+        VGR_IPT(radix_scatter_kernel)<<<g, t, 0, s>>>(ki, vi, ko, vo, d_n, shift, dbits, hist, tot, stride);
+#undef VGR_IPT
         shift += dbits;
         uint32_t *tt;
         tt = ki; ki = ko; ko = tt;
