@@ -153,7 +153,7 @@ __device__ __forceinline__ float pre_margin(const PreRec &r, float pxc, float py
     return __fmaf_rn(-dy, __fmaf_rn(r.Q11, dy, f1), g0);
 }
 
-// Index of the lowest bit of m (31 for m = 0).
+// Index of the lowest bit of m (31 for m = 0: the caller sees to what it reads there).
 __device__ __forceinline__ int lowest_bit(uint64_t m)
 {
     uint32_t lo, hi;
@@ -257,6 +257,12 @@ __device__ __forceinline__ void walk_tile_fwd(const RenderParams &rp, const Buff
     const float amin = rp.amin, amax = rp.amax;
     const float zn = vi.znear;
 
+    // A lane with no record left steps on slot 31 (lowest_bit), which a batch of fewer
+    // records has not written: its weight is 0, so the colour there has to be finite.
+    // Once a colour is not, every step takes the colour by whether the lane blends.
+    if (lane < B) st.g[5][lane] = make_float4(0, 0, 0, 0);
+    bool anyodd = false;   // of the list so far (uniform)
+
     // the staged records' items, a batch ahead
     uint32_t item = 0;
     if (lane < B && range.x + lane < range.y) item = b.inst_val[range.x + lane];
@@ -276,11 +282,13 @@ __device__ __forceinline__ void walk_tile_fwd(const RenderParams &rp, const Buff
         }
         if (keep) {
             const float4 c = stage_record(st, b, at, item, wild);
-            odd = BLOCKS && !(fabsf(c.x) + fabsf(c.y) + fabsf(c.z) < INFINITY);
+            odd = !(fabsf(c.x) + fabsf(c.y) + fabsf(c.z) < INFINITY);
             if constexpr (CULL) st.item[at] = (uint32_t)lane;   // its entry in the batch
         }
         if (lane < B && j + B < range.y) item = b.inst_val[j + B];
         const bool bad = wave_any(wild);   // the batch's records pass the pre-test untested
+        const bool oddb = wave_any(odd);
+        anyodd = anyodd || oddb;
         __syncthreads();
         {
             // Phase 1: bound pre-test of the whole batch (broadcast records);
@@ -385,9 +393,17 @@ __device__ __forceinline__ void walk_tile_fwd(const RenderParams &rp, const Buff
                     const uint64_t dom = blm & ~low;
                     const bool dob = __builtin_amdgcn_inverse_ballot_w64(dom);
                     const float wgt = dob ? wa * T[k] : 0.0f;
-                    C0[k] = __fmaf_rn(fr.c0, wgt, C0[k]);
-                    C1[k] = __fmaf_rn(fr.c1, wgt, C1[k]);
-                    C2[k] = __fmaf_rn(fr.c2, wgt, C2[k]);
+                    float c0 = fr.c0, c1 = fr.c1, c2 = fr.c2;
+                    if (__builtin_expect(anyodd, 0)) {
+                        // (the empty asm keeps this a branch)
+                        asm volatile("" : "+v"(c0), "+v"(c1), "+v"(c2));
+                        c0 = dob ? c0 : 0.0f;
+                        c1 = dob ? c1 : 0.0f;
+                        c2 = dob ? c2 : 0.0f;
+                    }
+                    C0[k] = __fmaf_rn(c0, wgt, C0[k]);
+                    C1[k] = __fmaf_rn(c1, wgt, C1[k]);
+                    C2[k] = __fmaf_rn(c2, wgt, C2[k]);
                     T[k] = dob ? Tn : T[k];
                     alive[k] &= ~(blm & low);
                     if constexpr (BLOCKS) {
@@ -411,7 +427,7 @@ __device__ __forceinline__ void walk_tile_fwd(const RenderParams &rp, const Buff
                     if (anyclamp) b.qclamp[bq * 16 + word] = over;
                     if (wave_any(mine != 0)) used = (bs - range.x) / B + 1;
                     last[k] = mine != 0 ? (int)bs + 63 - (int)__builtin_clzll(mine) : last[k];
-                    const uint32_t flag = (anyclamp ? kFlagClamp : 0u) | (wave_any(odd) ? kFlagOdd : 0u);
+                    const uint32_t flag = (anyclamp ? kFlagClamp : 0u) | (oddb ? kFlagOdd : 0u);
                     if (lane < 4) b.qflag[bq + lane] = flag;
                 }
             }

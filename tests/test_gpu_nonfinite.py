@@ -1,0 +1,58 @@
+"""Values that are not finite reach only the pixels and Gaussians that they belong to.
+
+The colour rasterisers multiply by a weight of zero where a lane has nothing to
+blend, and 0 * Inf is NaN: a colour, a weight or an upstream gradient that is not
+finite must not get into such a product with another pixel's sums.  One small
+view alone takes the rasterisers' way by 4x4 blocks, 63 equal views in one call
+(over 8192 8x8 regions) the way by regions.
+"""
+import numpy as np
+import pytest
+
+import gpu_helpers as G
+import helpers as H
+from paper_2412_03378_amd import scenes
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def _setup():
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    from paper_2412_03378_amd import Renderer
+    return Renderer(0), torch.device("cuda", 0)
+
+
+@pytest.mark.parametrize("model,tile,batch", [
+    ("volumetric", (8, 8), 64), ("volumetric", (16, 16), 64), ("volumetric", (32, 8), 64),
+    ("splat", (8, 8), 64), ("splat", (8, 8), 32), ("splat", (16, 8), 64), ("splat", (16, 16), 32),
+    ("splat", (32, 8), 64)])
+def test_leftovers_of_another_frame(model, tile, batch):
+    """A frame of short lists after one whose staged colours were all infinite: what
+    the kernels before it left in the LDS does not show."""
+    R, dev = _setup()
+    from paper_2412_03378_amd import Settings
+    w, h = 1280, 1024            # 20480 regions of 8x8
+    cam = scenes.axis_camera(3.0, w, h, 45.0)
+    st = Settings(tile=tile, batch=batch, alpha_model=model, bg=(0.2, 0.1, 0.3))
+    rng = np.random.default_rng(5)
+    # 96 faint Gaussians over the whole frame, infinite colours
+    n = 96
+    faint = 0.01 if model == "splat" else 0.002
+    full = H.scene(np.c_[rng.uniform(-0.1, 0.1, (n, 2)), rng.uniform(0.0, 0.5, n)], 2.0, faint)
+    full.sh[:] = np.inf
+    # a few entries per list
+    m = 4000
+    few = H.scene(np.c_[rng.uniform(-1.2, 1.2, (m, 2)), rng.uniform(-0.2, 0.2, m)],
+                  rng.uniform(0.005, 0.02, (m, 3)),
+                  rng.uniform(0.1, 0.9, m) if model == "splat" else rng.uniform(5.0, 60.0, m),
+                  quats=rng.standard_normal((m, 4)), rgb=rng.uniform(0, 1, (m, 3)))
+    t_full, t_few = G.device_scene(full, dev), G.device_scene(few, dev)
+    for _ in range(4):
+        flood = R.forward(*t_full, [cam], st)[0]
+        img = R.forward(*t_few, [cam], st)[0]
+        torch.cuda.synchronize()
+        assert torch.isinf(flood).all()
+        assert torch.isfinite(img).all(), int((~torch.isfinite(img)).sum())
