@@ -235,7 +235,8 @@ __device__ __forceinline__ void block_fwd(const RenderParams &rp, const Buffers 
     float T = 1.0f, C = 0.0f;   // C: channel r
     int last = -1;
     // colours past a batch's survivors are read (with no lane blending), so they
-    // have to be finite
+    // have to be finite: they are zeros or an earlier batch's, and zeros again after a
+    // batch with one that is not finite
     st.c[lane] = make_float4(0, 0, 0, 0);
     uint64_t alive = __builtin_amdgcn_ballot_w64(inside);   // uniform
     uint32_t used = 0;                                      // batches up to the last that blended
@@ -398,6 +399,7 @@ __device__ __forceinline__ void block_fwd(const RenderParams &rp, const Buffers 
             if (anyclamp) b.qclamp[bq * 16 + p] = over;
         }
         if (lane == 0) b.qflag[bq] = (anyclamp ? kFlagClamp : 0u) | (anyodd ? kFlagOdd : 0u);
+        if (anyodd) st.c[lane] = make_float4(0, 0, 0, 0);
         __syncthreads();
     }
 

@@ -56,3 +56,47 @@ def test_leftovers_of_another_frame(model, tile, batch):
         torch.cuda.synchronize()
         assert torch.isinf(flood).all()
         assert torch.isfinite(img).all(), int((~torch.isfinite(img)).sum())
+
+
+def _settings(tile, option):
+    from paper_2412_03378_amd import Settings
+    return Settings(tile=tile, bg=(0.2, 0.1, 0.3), near_segment=option == "near",
+                    kernel="epanechnikov" if option == "epanechnikov" else "gaussian",
+                    alpha_model="splat" if option == "splat" else "volumetric")
+
+
+def _cloud(rng, n, bad_color):
+    """Lists of several batches that no pixel leaves early; every fiftieth Gaussian is
+    small and of the given colour."""
+    means = rng.normal(0.0, 0.3, (n, 3))
+    scales = np.exp(rng.uniform(np.log(0.01), np.log(0.05), (n, 3)))
+    dens = np.exp(rng.uniform(np.log(0.2), np.log(2.0), n))
+    rgb = rng.uniform(0.1, 1, (n, 3))
+    quats = rng.standard_normal((n, 4))
+    scales[::50] = 0.008
+    dens[::50] = 20.0
+    rgb[::50] = bad_color
+    return H.scene(means, scales, dens, quats=quats, rgb=rgb)
+
+
+@pytest.mark.parametrize("views", [1, 63])
+@pytest.mark.parametrize("option", ["gaussian", "near", "epanechnikov", "splat"])
+@pytest.mark.parametrize("tile", [(8, 8), (16, 16), (32, 8)])
+def test_infinite_colours(tile, option, views):
+    """Pixels that blend none of the infinite colours equal the image with finite ones."""
+    R, dev = _setup()
+    w, h, n = 123, 91, 3000
+    cam = scenes.axis_camera(3.0, w, h, 45.0)
+    st = _settings(tile, option)
+
+    def image(color):
+        sc = _cloud(np.random.default_rng(n), n, color)
+        if option == "splat":
+            sc.dens[:] = 1.0 - np.exp(-0.05 * sc.dens)
+        return R.forward(*G.device_scene(sc, dev), [cam] * views, st)[-1].clone()
+
+    far, img, bad = image(100.0), image(0.7), image(np.inf)
+    blends = (far != img).any(0)               # pixels that blend one of them
+    assert 0 < int(blends.sum()) < blends.numel() // 2
+    assert torch.equal(bad[:, ~blends], img[:, ~blends])
+    assert not torch.isfinite(bad[:, blends]).any()
