@@ -346,16 +346,18 @@ __device__ __forceinline__ void block_fwd(const RenderParams &rp, const Buffers 
                 const float T1 = T * quad_bcast<0>(oe), T2 = T1 * quad_bcast<1>(oe);
                 const float T3 = T2 * quad_bcast<2>(oe), T4 = T3 * quad_bcast<3>(oe);
                 const float Tb = quad_pick(qm, T, T1, T2, T3);
-                const uint64_t stop = __builtin_amdgcn_ballot_w64(T4 < Tmin);
+                const uint64_t stop = __builtin_amdgcn_ballot_w64(!(T4 >= Tmin));
                 if (__builtin_expect(stop == 0, 1)) {
                     T = T4;
-                } else {   // T keeps the last value not below Tmin
-                    bm &= __builtin_amdgcn_ballot_w64(!(Tb * oe < Tmin));
-                    if (!(T4 < Tmin)) T = T4;
-                    else if (!(T3 < Tmin)) T = T3;
-                    else if (!(T2 < Tmin)) T = T2;
-                    else if (!(T1 < Tmin)) T = T1;
-                    alive &= ~stop;
+                } else {
+                    // T keeps the last value before the first one below Tmin, where the
+                    // pixel stops: what is behind it, NaN (a line integral of Inf * 0)
+                    // included, does not count
+                    const bool s1 = T1 < Tmin, s2 = s1 || T2 < Tmin, s3 = s2 || T3 < Tmin;
+                    const bool s4 = s3 || T4 < Tmin;
+                    bm &= __builtin_amdgcn_ballot_w64(!(r == 0 ? s1 : (r == 1 ? s2 : (r == 2 ? s3 : s4))));
+                    T = s1 ? T : (s2 ? T1 : (s3 ? T2 : (s4 ? T3 : T4)));
+                    alive &= ~__builtin_amdgcn_ballot_w64(s4);
                     if (alive == 0) lim = 0;   // every pixel has stopped
                 }
                 const bool dob = __builtin_amdgcn_inverse_ballot_w64(bm);

@@ -100,3 +100,30 @@ def test_infinite_colours(tile, option, views):
     assert 0 < int(blends.sum()) < blends.numel() // 2
     assert torch.equal(bad[:, ~blends], img[:, ~blends])
     assert not torch.isfinite(bad[:, blends]).any()
+
+
+@pytest.mark.parametrize("views", [1, 63])
+@pytest.mark.parametrize("front", [1, 2, 3, 4])
+def test_overflow_behind_a_stopped_pixel(front, views):
+    """Opaque Gaussians stop every pixel; behind them one whose line integral overflows
+    to Inf * 0.  Its place in the step of four in which the pixels stop does not
+    matter."""
+    R, dev = _setup()
+    from paper_2412_03378_amd import Settings
+    w, h = 123, 91
+    cam = scenes.axis_camera(3.0, w, h, 45.0)
+    st = Settings(tile=(8, 8), bg=(0.2, 0.1, 0.3), T_min=0.02)
+    # front - 1 faint ones, one that leaves T = 0.01 < T_min, the one that overflows
+    n = front + 1
+    means = np.c_[np.zeros((n, 2)), np.linspace(0.0, 0.5, n)]
+    dens = np.full(n, 0.01)
+    dens[front - 1] = 1e4
+    dens[front] = 3e38
+    scales = np.full((n, 3), 3.0)
+    scales[front] = 0.05
+    t = G.device_scene(H.scene(means, scales, dens, rgb=np.linspace(0.2, 0.9, n)[:, None]), dev)
+    want = R.forward(*[x[:front].contiguous() for x in t], [cam] * views, st)[-1].clone()
+    img = R.forward(*t, [cam] * views, st)[-1]
+    torch.cuda.synchronize()
+    assert torch.isfinite(want).all()
+    assert torch.equal(img, want)
