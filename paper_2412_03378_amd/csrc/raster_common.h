@@ -54,6 +54,13 @@ __device__ __forceinline__ uint32_t cu_key()
 // which the branch tests directly.
 __device__ __forceinline__ bool wave_any(bool p) { return __builtin_amdgcn_ballot_w64(p) != 0; }
 
+// Whether products of two such triples stay finite, so that a weight of 0 takes them
+// out of a sum.
+__device__ __forceinline__ bool ordinary(float x, float y, float z)
+{
+    return fabsf(x) + fabsf(y) + fabsf(z) < 1e18f;
+}
+
 __device__ __forceinline__ int find_view(const ViewInfo *views, int n_views, int gt)
 {
     int v = 0;

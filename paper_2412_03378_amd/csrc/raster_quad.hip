@@ -278,7 +278,7 @@ __device__ __forceinline__ void block_fwd(const RenderParams &rp, const Buffers 
         const uint32_t j = bs + lane;
         const uint64_t km = km1;
         const int cnt = __builtin_popcountll(km);
-        bool odd = false;   // a colour that is not finite
+        bool odd = false;   // a colour that is not finite, or huge
         if (__builtin_amdgcn_inverse_ballot_w64(km)) {
             const int at = __builtin_popcountll(km & below);
             st.h[at] = rec.h;
@@ -290,7 +290,7 @@ __device__ __forceinline__ void block_fwd(const RenderParams &rp, const Buffers 
             c[4] = rec.g5.y;
             c[8] = rec.g5.z;
             if constexpr (NEAR) st.mz[at] = rec.g5.w;
-            odd = !(fabsf(rec.g5.x) + fabsf(rec.g5.y) + fabsf(rec.g5.z) < INFINITY);
+            odd = !ordinary(rec.g5.x, rec.g5.y, rec.g5.z);
         }
         if (lane < 4) {   // the pad: |w| = 1 and K' = 0, which blends nowhere
             st.h[cnt + lane] = st.a[cnt + lane] = st.v[cnt + lane] = make_float4(0, 0, 0, 0);
@@ -310,7 +310,7 @@ __device__ __forceinline__ void block_fwd(const RenderParams &rp, const Buffers 
         __syncthreads();
         // entries of the batch that the lane blended, and of those it clamped
         uint64_t mine = 0, over = 0;
-        // ODD: some colour of the batch is not finite; it reaches only the pixels
+        // ODD: some colour of the batch is not ordinary; it reaches only the pixels
         // that blend it
         auto steps = [&](auto ODD) {
             int lim = cnt;
@@ -654,6 +654,8 @@ __device__ __forceinline__ void blocks_bwd(const RenderParams &rp, const Buffers
         };
         load_masks(top - 1);
         advance(top - 1);
+        // (after the batch's loads are under way)
+        bool wild = wave_any(!ordinary(g0, g1, g2) || !(fabsf(GB) < INFINITY));   // uniform
         for (int kb = top - 1; kb >= 0; --kb) {
             if (__builtin_amdgcn_inverse_ballot_w64(kany)) {
                 const float vx = rec.g3.w, vy = rec.g4.x, vz = rec.g4.y;
@@ -674,8 +676,12 @@ __device__ __forceinline__ void blocks_bwd(const RenderParams &rp, const Buffers
                 st.c[lane] = make_float4(rec.g5.x, rec.g5.y, rec.g5.z, __uint_as_float(itr));
                 if constexpr (NEAR) st.e[lane] = make_float4(mz * (V2 * iV), V2 * iV, 0, 0);
             }
-            // SPECIAL: a pair of the batch was clamped or has a colour that is not finite
-            const bool special = flags != 0;   // uniform
+            // CLAMP: a pair of the batch was clamped.  WILD: a colour of the list so far or
+            // an upstream gradient is not ordinary; what a pixel does not blend is left
+            // out by selects, since a weight of 0 does not take it, or what its GB has
+            // become, out
+            wild = wild || (flags & kFlagOdd) != 0;
+            const bool special = wild || flags != 0;   // uniform
             const uint64_t cur = mask, curc = cmask, touched = kany;
             const uint32_t clo = klo, chi = khi;
             advance(kb - 1);
@@ -703,7 +709,7 @@ __device__ __forceinline__ void blocks_bwd(const RenderParams &rp, const Buffers
                     if (special) cm = lane_from(curc, 16 * k + p);
                 }
                 lds_wave_sync();
-                auto steps = [&](auto SPECIAL) {
+                auto steps = [&](auto CLAMP, auto WILD) {
                 for (int s = (cnt + 3) / 4 - 1; s >= 0; --s) {
                     const uint32_t off = st.off[4 * s + r];
                     const char *rb = reinterpret_cast<const char *>(st.h) + off;
@@ -752,7 +758,7 @@ __device__ __forceinline__ void blocks_bwd(const RenderParams &rp, const Buffers
                     y = bl ? y : 0.0f;
                     bool clamped = false;
                     float ye = y;
-                    if constexpr (SPECIAL) {
+                    if constexpr (CLAMP) {
                         clamped = bl && ((cm >> (off >> 4)) & 1u) != 0;
                         ye = clamped ? ymax : y;
                     }
@@ -764,7 +770,7 @@ __device__ __forceinline__ void blocks_bwd(const RenderParams &rp, const Buffers
                     const float Tb = quad_pick(qm, T0, T1, T2, T3);
                     T = T0;
                     float gc = __fmaf_rn(g0, rc.x, __fmaf_rn(g1, rc.y, g2 * rc.z));
-                    if constexpr (SPECIAL) gc = bl ? gc : 0.0f;
+                    if constexpr (WILD) gc = bl ? gc : 0.0f;
                     const float wgt = (1.0f - om) * Tb;
                     const float gw = gc * wgt;
                     const float G2 = GB + quad_bcast<3>(gw), G1 = G2 + quad_bcast<2>(gw);
@@ -774,11 +780,17 @@ __device__ __forceinline__ void blocks_bwd(const RenderParams &rp, const Buffers
                     // dL/dalpha = T_before (g.c) - (g.B) / (1 - alpha)
                     const float da = __fmaf_rn(Tb, gc, -(inv * Gr));
                     float t = da * (kLn2 * om) * y;             // dL/d(ln x)
-                    if constexpr (SPECIAL) t = clamped ? 0.0f : t;
+                    if constexpr (CLAMP) t = clamped ? 0.0f : t;
                     float acc[16];
                     acc[10] = g0 * wgt;
                     acc[11] = g1 * wgt;
                     acc[12] = g2 * wgt;
+                    if constexpr (WILD) {
+                        acc[10] = bl ? acc[10] : 0.0f;
+                        acc[11] = bl ? acc[11] : 0.0f;
+                        acc[12] = bl ? acc[12] : 0.0f;
+                        t = bl ? t : 0.0f;
+                    }
                     acc[13] = acc[14] = acc[15] = 0.0f;
                     acc[9] = t;
                     if constexpr (!NEAR && !EPAN) {
@@ -835,8 +847,9 @@ __device__ __forceinline__ void blocks_bwd(const RenderParams &rp, const Buffers
                     }
                 }
                 };
-                if (special) steps(std::true_type{});
-                else steps(std::false_type{});
+                if (!special) steps(std::false_type{}, std::false_type{});
+                else if (!wild) steps(std::true_type{}, std::false_type{});
+                else steps(std::true_type{}, std::true_type{});
                 if (BPW == 4 && r == 0) st.run[16 * k + p] = make_float2(T, GB);
             }
             if constexpr (BPW == 4) {

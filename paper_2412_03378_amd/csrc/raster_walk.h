@@ -268,7 +268,7 @@ __device__ __forceinline__ void walk_tile_fwd(const RenderParams &rp, const Buff
     if (lane < B && range.x + lane < range.y) item = b.inst_val[range.x + lane];
     for (uint32_t bs = range.x; bs < range.y; bs += B) {
         const uint32_t j = bs + lane;
-        bool odd = false;   // a colour that is not finite
+        bool odd = false;   // a colour that is not finite, or huge
         bool wild = false;  // a pre-test field that is not
         int nb = (int)min((uint32_t)B, range.y - bs);
         bool keep = lane < B && j < range.y;
@@ -282,7 +282,7 @@ __device__ __forceinline__ void walk_tile_fwd(const RenderParams &rp, const Buff
         }
         if (keep) {
             const float4 c = stage_record(st, b, at, item, wild);
-            odd = !(fabsf(c.x) + fabsf(c.y) + fabsf(c.z) < INFINITY);
+            odd = !ordinary(c.x, c.y, c.z);
             if constexpr (CULL) st.item[at] = (uint32_t)lane;   // its entry in the batch
         }
         if (lane < B && j + B < range.y) item = b.inst_val[j + B];

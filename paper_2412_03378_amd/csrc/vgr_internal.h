@@ -222,7 +222,7 @@ __host__ __device__ inline size_t quad_batch(uint32_t start, int t)
     return (size_t)(start >> 6) + (size_t)t;
 }
 // qflag: some pair of the batch was clamped (qclamp is valid); some colour of the
-// batch is not finite.
+// batch is not finite, or huge.
 constexpr uint32_t kFlagClamp = 1u, kFlagOdd = 2u;
 // Most tiles the colour rasterisers treat as long (one wave per 4x4 block, the first
 // d_total[3] of tile_order): 2048 regions of 8x8 pixels, whose 8192 waves fill the

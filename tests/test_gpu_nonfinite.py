@@ -127,3 +127,79 @@ def test_overflow_behind_a_stopped_pixel(front, views):
     torch.cuda.synchronize()
     assert torch.isfinite(want).all()
     assert torch.equal(img, want)
+
+
+@pytest.mark.parametrize("views", [1, 63])
+@pytest.mark.parametrize("option", ["gaussian", "near", "epanechnikov"])
+@pytest.mark.parametrize("tile", [(8, 8), (16, 16)])
+def test_gradients_beside_infinite_colours(tile, option, views):
+    """Gaussians that share no pixel with the infinite colours have the gradients of
+    the scene with finite ones."""
+    R, dev = _setup()
+    w, h, n = 123, 91, 3000
+    cam = scenes.axis_camera(3.0, w, h, 45.0)
+    st = _settings(tile, option)
+
+    def forward(color):
+        t = G.device_scene(_cloud(np.random.default_rng(n), n, color), dev)
+        return t, R.forward(*t, [cam] * views, st)[-1].clone()
+
+    def grads(t, dL):
+        g = [torch.zeros_like(x) for x in t]
+        R.backward([dL] * views, *g)
+        return [x.cpu().numpy().reshape(n, -1).astype(np.float64) for x in g]
+
+    _, far = forward(100.0)
+    t, img = forward(0.7)
+    blends = (far != img).any(0)
+    # Gaussians that some such pixel blends (their colours get a gradient from it)
+    ones = blends.float()[None].expand(3, -1, -1).contiguous()
+    apart = (grads(t, ones)[4] == 0.0).all(1)
+    assert 0 < int(apart.sum()) < n
+    rng = np.random.default_rng(1)
+    dL = torch.from_numpy(rng.standard_normal((3, h, w)).astype(np.float32)).to(dev) * ~blends
+    want = grads(t, dL)
+    t, _ = forward(np.inf)
+    got = grads(t, dL)
+    for k, a, b in zip(G.GRAD_KEYS, got, want):
+        # (the FP32 sums of a Gaussian's pixels in another order)
+        assert np.isfinite(a[apart]).all(), k
+        assert np.all(np.abs(a - b)[apart] <= G.GRAD_REL * np.abs(b[apart]).max()), k
+
+
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+@pytest.mark.parametrize("views", [1, 63])
+@pytest.mark.parametrize("option", ["gaussian", "near", "epanechnikov"])
+def test_upstream_gradient_of_one_pixel(option, views, value):
+    """Two Gaussians of one pixel each in every 8x8 region, both in its first 4x4
+    block.  An upstream gradient that is not finite at the first one's pixel leaves
+    the gradients of the second alone."""
+    R, dev = _setup()
+    w, h = 123, 91
+    cam = scenes.axis_camera(3.0, w, h, 45.0)
+    st = _settings((8, 8), option)
+    px, py = np.meshgrid(np.arange(0, w - 7, 8), np.arange(0, h - 7, 8))
+    first = np.c_[px.ravel(), py.ravel()]
+    pix = np.r_[first, first + [2, 3]]
+    mean = np.c_[(pix + 0.5 - [cam.cx, cam.cy]) * 3.0 / [cam.fx, cam.fy], np.zeros(len(pix))]
+    # sigma 0.2 pixels, alpha 0.3 at the centre: no other pixel centre reaches 1/255
+    s = 0.2 * 3.0 / cam.fx
+    sc = H.scene(mean, s, 0.36 / (s * np.sqrt(2 * np.pi)), rgb=(0.6, 0.3, 0.8))
+    t = G.device_scene(sc, dev)
+    dL = torch.ones((3, h, w), device=dev)
+
+    def grads(dL):
+        imgs = R.forward(*t, [cam] * views, st)
+        assert int((imgs[0][0] != imgs[0][0, 1, 1]).sum()) == len(pix)
+        g = [torch.zeros_like(x) for x in t]
+        R.backward([dL] * views, *g)
+        return [x.cpu().numpy().reshape(len(pix), -1).astype(np.float64) for x in g]
+
+    want = grads(dL)
+    dL[:, first[:, 1], first[:, 0]] = value
+    got = grads(dL)
+    m = len(first)
+    for k, a, b in zip(G.GRAD_KEYS, got, want):
+        # one pixel a view: the sums differ in the order of equal terms only
+        assert np.allclose(a[m:], b[m:], rtol=1e-5, atol=1e-5 * np.abs(b).max()), k
+    assert not np.isfinite(got[3][:m]).any()
