@@ -22,8 +22,9 @@ ARCH = os.environ.get("VGR_OFFLOAD_ARCH", "gfx950")
 HIPCC_FLAGS = [
     f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC",
     "-munsafe-fp-atomics",
-    # no implicit contraction: the backward recomputes the forward's decisions
-    # bit for bit, so every fused multiply-add in the kernels is written out
+    # no implicit contraction: a value that two kernels form (the frame of the
+    # moments, a pair's integral where a decision is taken again) has the same
+    # bits in both, so every fused multiply-add in the kernels is written out
     "-ffp-contract=off",
     # packed FP32 VALU forms are kept out of the generated code
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

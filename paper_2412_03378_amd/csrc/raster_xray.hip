@@ -28,7 +28,8 @@
 //     formula does: a value within kTie of the cut (one visit in 200) is evaluated
 //     again in the L-frame, from the rest of the record.
 //
-// Backward: lane l holds an entry.  Entries that reach a slot are packed in LDS, and 64
+// Backward (it takes the forward's decisions, with the same band around the cut): lane l
+// holds an entry.  Entries that reach a slot are packed in LDS, and 64
 // of them run over the slot's 64 pixels, whose dL/dx and cut are broadcast from LDS; a
 // lane sums its own record's moments, so nothing is reduced over lanes (a sum of ten
 // values over a wave costs as much as a pair).  Along a row a1 is constant, so the
@@ -75,6 +76,7 @@ __device__ __forceinline__ RayRec load_ray(RecPtr p)
 // Relative band around the cut in which the L-frame decides: far above the rounding
 // of either formula.
 constexpr float kTie = 1.0f / 1024;
+constexpr float kMost = (1.0f - kTie) / (1.0f + kTie);   // its lower end over its upper
 
 template <int MODE>
 struct Kind {
@@ -119,11 +121,12 @@ __device__ __forceinline__ float length_v0(const V4 &g4, const V4 &g5)
     return __builtin_amdgcn_sqrtf(__fmaf_rn(g4.z, g4.z, __fmaf_rn(g4.w, g4.w, g5.x * g5.x)));
 }
 
-// log2(e) x of a pair by the L-frame formula of the colour kernels.
-template <int MODE>
-__device__ __forceinline__ float lframe_y(RecPtr rec, float dx, float dy, float un, float zn)
+// log2(e) x of a pair by the L-frame formula of the colour kernels, from a record's g3
+// to g5.
+template <int MODE, class V4>
+__device__ __forceinline__ float lframe_y(const V4 &g3, const V4 &g4, const V4 &g5, float dx,
+                                          float dy, float un, float zn)
 {
-    const vec4 g3 = rec[3], g4 = rec[4], g5 = rec[5];
     const float A00 = g3.x, A10 = g3.y, A20 = g3.z, A01 = g3.w, A11 = g4.x, A21 = g4.y;
     const float v0x = g4.z, v0y = g4.w, v0z = g5.x, K = g5.y, se = g5.z, mz = g5.w;
     const float a0 = __fmaf_rn(A01, dy, A00 * dx);
@@ -170,12 +173,13 @@ struct TileWave {
     {
         return slot_x(k) < vi->width && slot_y(k) < vi->height;
     }
-    __device__ __forceinline__ float unit(int k) const
+    __device__ __forceinline__ float unit(int px, int py) const   // |u| of a pixel
     {
-        const float ux = ((float)x(k) + 0.5f - vi->cx) / vi->fx;
-        const float uy = ((float)y(k) + 0.5f - vi->cy) / vi->fy;
+        const float ux = ((float)px + 0.5f - vi->cx) / vi->fx;
+        const float uy = ((float)py + 0.5f - vi->cy) / vi->fy;
         return sqrtf(ux * ux + uy * uy + 1.0f);
     }
+    __device__ __forceinline__ float unit(int k) const { return unit(x(k), y(k)); }
 };
 
 // The lanes' candidates, a batch ahead: item and culling ellipse.
@@ -326,7 +330,7 @@ __global__ __launch_bounds__(512) void xray_fwd_kernel(RenderParams rp, Buffers 
                 uint64_t on = __builtin_amdgcn_ballot_w64(y > sure[k]);
                 const uint64_t may = __builtin_amdgcn_ballot_w64(!(y < most[k]));
                 if (__builtin_expect(on != may, 0)) {
-                    const float yl = lframe_y<MODE>(rec, dx[ix], dy[iy], t.unit(k), zn);
+                    const float yl = lframe_y<MODE>(rec[3], rec[4], rec[5], dx[ix], dy[iy], t.unit(k), zn);
                     on |= __builtin_amdgcn_ballot_w64(!(yl < tau2)) & may &
                           __builtin_amdgcn_ballot_w64(t.in(k));
                 }
@@ -385,13 +389,16 @@ template <int N, int NSLOT>
 struct BwdWave {
     static constexpr int kAcc = NSLOT == 16 ? 17 : 11;   // odd: rows on different banks
     uint32_t queue[N][128];    // entries that reach slot k and have not run
-    float2 pix[N][64];         // dL/dx x / y, cut of y / |u|
+    float2 pix[N][64];         // dL/dx x / y, least sure y / |u|
     float acc[64 * kAcc];
     uint32_t item[64];
 };
 
+// Five waves per SIMD: left alone the compiler takes four (64 views of 16x16 tiles 2 %
+// slower, 16x8 tiles 8 %).
 template <int TW, int TH, int MODE, bool COUNT>
-__global__ __launch_bounds__(512) void xray_bwd_kernel(RenderParams rp, Buffers b)
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(5))) void xray_bwd_kernel(
+    RenderParams rp, Buffers b)
 {
     using S = Slots<TW, TH>;
     constexpr bool NEAR = Kind<MODE>::NEAR, EPAN = Kind<MODE>::EPAN;
@@ -412,13 +419,13 @@ __global__ __launch_bounds__(512) void xray_bwd_kernel(RenderParams rp, Buffers 
     for (int k = 0; k < S::N; ++k) {
         const float un = t.unit(k);
         const float dL = t.in(k) ? t.vi->dL[(int64_t)t.y(k) * t.vi->width + t.x(k)] : 0.0f;
-        st.pix[k][lane] = make_float2(dL * (kLn2 * un), tau2 / un);
+        st.pix[k][lane] = make_float2(dL * (kLn2 * un), tau2 / un * (1.0f + kTie));
     }
 
-    // The first m entries of slot k's queue over its pixels.
-    auto run = [&](int k, int m) {
+    // The first cnt entries of slot k's queue over its pixels.
+    auto run = [&](int k, int cnt) {
         lds_wave_sync();
-        const uint32_t it = st.queue[k][lane < m ? lane : 0];
+        const uint32_t it = st.queue[k][lane < cnt ? lane : 0];
         const float4 *gp = b.geom + (size_t)it * kRecVec;
         const float4 h = gp[0], r = gp[1], s = gp[2];
         const float E = EPAN ? s.w : s.w * (2.0f / kLog2e);
@@ -438,94 +445,134 @@ __global__ __launch_bounds__(512) void xray_bwd_kernel(RenderParams rp, Buffers 
         float acc[16];
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[e] = 0.0f;
+        // A pair's geometry, D^2 (scaled, unless EPAN) and y / |u|.
+        struct Term {
+            RayPair g;
+            float hp, d2, yy, hh, hn;   // hh, hn: as in raster_quad.hip
+        };
+        auto term = [&](float dxx, float a0r, float a1, float a1sq, float wr) {
+            Term m;
+            m.g = ray_pair(__fmaf_rn(r.x, dxx, a0r), a1, a1sq, __fmaf_rn(s.x, dxx, wr));
+            m.hp = m.g.h * m.g.rq2;
+            m.d2 = s.w * m.hp;   // (log2 e / 2) D^2, or D^2 (EPAN)
+            float ex;
+            if constexpr (EPAN) {
+                const float h2 = fmaxf(1.0f - m.d2, 0.0f);
+                ex = h2 * __builtin_amdgcn_sqrtf(h2);
+            } else {
+                ex = fast_exp2(-m.d2);
+            }
+            m.yy = (NEAR ? fabsf(s.z) : s.z) * (m.g.rq * ex);
+            m.hh = m.hn = 0.0f;
+            if constexpr (NEAR) {
+                if (s.z < 0.0f) {
+                    float zw;
+                    const float eta = ray_eta(V, mz, m.g, zn, zw);
+                    const float Phi = norm_cdf(eta);
+                    m.yy *= Phi;
+                    m.hh = Phi > 1e-30f ? 0.39894228f * fast_exp2(-0.72134752f * eta * eta) / Phi : -eta;
+                    m.hn = m.hh * __fmaf_rn(2.0f, zw, eta);
+                }
+            }
+            return m;
+        };
+        // PLAIN: a row's sums, whose factors a1 and a1^2 come in at its end.
+        struct Row {
+            float S0 = 0.0f, S1 = 0.0f, SW = 0.0f, L0 = 0.0f, L1 = 0.0f, LW = 0.0f;
+        };
+        // tt: dL/d(ln x)
+        auto add = [&](Row &q, const Term &m, float tt) {
+            const RayPair &g = m.g;
+            acc[9] += tt;
+            if constexpr (PLAIN) {
+                const float T = tt * g.rq2;
+                const float L = T * __fmaf_rn(m.d2, -2.0f / kLog2e, 1.0f);
+                const float T0 = T * g.a0, La = L * g.a0;
+                q.S0 += T;
+                q.S1 += T0;
+                q.SW = __fmaf_rn(T, g.w2, q.SW);
+                acc[0] = __fmaf_rn(T0, g.a0, acc[0]);
+                acc[3] = __fmaf_rn(T0, g.w2, acc[3]);
+                q.L0 += L;
+                q.L1 += La;
+                q.LW = __fmaf_rn(L, g.w2, q.LW);
+                acc[5] = __fmaf_rn(La, g.a0, acc[5]);
+                acc[8] = __fmaf_rn(La, g.w2, acc[8]);
+            } else {
+                // weights of p p^T (tw) and of the z terms (tz)
+                const float D2 = EPAN ? m.d2 : m.d2 * (2.0f / kLog2e);
+                const float p0 = g.a0 * g.rq, p1 = g.a1 * g.rq, p2 = g.w2 * g.rq;
+                float tw = tt, tz = tt;
+                if constexpr (EPAN) tz = tt != 0.0f ? tt * (3.0f * fast_rcp(1.0f - D2)) : 0.0f;
+                if constexpr (NEAR) {
+                    tw = __fmaf_rn(tt, m.hn, tt);
+                    const float th = tt * m.hh;
+                    acc[13] = __fmaf_rn(th, p0, acc[13]);
+                    acc[14] = __fmaf_rn(th, p1, acc[14]);
+                    acc[15] = __fmaf_rn(th, p2, acc[15]);
+                }
+                const float kp = __fmaf_rn(tz, E - D2, tw), kq = __fmaf_rn(-tz, D2, tw);
+                const float z0 = tz * p0, z1 = tz * p1, zh = tz * m.hp;
+                acc[0] = __fmaf_rn(kp * p0, p0, acc[0]);
+                acc[1] = __fmaf_rn(kp * p0, p1, acc[1]);
+                acc[2] = __fmaf_rn(kq * p0, p2, acc[2]);
+                acc[3] = __fmaf_rn(kp * p1, p1, acc[3]);
+                acc[4] = __fmaf_rn(kq * p1, p2, acc[4]);
+                acc[5] += __fmaf_rn(-tw, p2 * p2, __fmaf_rn(-zh, D2, tt));   // sum t - M_22
+                acc[6] = __fmaf_rn(z0, p2, acc[6]);
+                acc[7] = __fmaf_rn(z1, p2, acc[7]);
+                acc[8] += zh;
+            }
+        };
+        auto end_row = [&](const Row &q, float a1, float a1sq) {
+            if constexpr (PLAIN) {
+                acc[1] = __fmaf_rn(q.S1, a1, acc[1]);
+                acc[2] = __fmaf_rn(q.S0, a1sq, acc[2]);
+                acc[4] = __fmaf_rn(q.SW, a1, acc[4]);
+                acc[6] = __fmaf_rn(q.L1, a1, acc[6]);
+                acc[7] = __fmaf_rn(q.L0, a1sq, acc[7]);
+                acc[10] = __fmaf_rn(q.LW, a1, acc[10]);
+            }
+        };
+        uint64_t tied = 0;   // bit 8 y + x: a pair within kTie of the cut (uniform)
         for (int y = 0; y < ny; ++y) {
             const float dy = ((float)(t.slot_y(k) + y) + 0.5f - h.y) - h.w;
             const float a0r = r.y * dy, a1 = r.z * dy, a1sq = a1 * a1;
             const float wr = __fmaf_rn(s.y, dy, 1.0f);
-            float S0 = 0.0f, S1 = 0.0f, SW = 0.0f, L0 = 0.0f, L1 = 0.0f, LW = 0.0f;
             const float2 *px = &st.pix[k][y * kRegion];
+            Row q;
+            uint32_t cols = 0;
 #pragma unroll
             for (int x = 0; x < kRegion; ++x) {
                 if (x >= nx) break;   // uniform
                 const float2 gc = px[x];
-                const RayPair g = ray_pair(__fmaf_rn(r.x, dx[x], a0r), a1, a1sq,
-                                           __fmaf_rn(s.x, dx[x], wr));
-                const float hp = g.h * g.rq2;
-                const float d2 = s.w * hp;   // (log2 e / 2) D^2, or D^2 (EPAN)
-                float ex;
-                if constexpr (EPAN) {
-                    const float h2 = fmaxf(1.0f - d2, 0.0f);
-                    ex = h2 * __builtin_amdgcn_sqrtf(h2);
-                } else {
-                    ex = fast_exp2(-d2);
-                }
-                float yy = (NEAR ? fabsf(s.z) : s.z) * (g.rq * ex);
-                float hh = 0.0f, hn = 0.0f;   // as in raster_quad.hip
-                if constexpr (NEAR) {
-                    if (s.z < 0.0f) {
-                        float zw;
-                        const float eta = ray_eta(V, mz, g, zn, zw);
-                        const float Phi = norm_cdf(eta);
-                        yy *= Phi;
-                        hh = Phi > 1e-30f ? 0.39894228f * fast_exp2(-0.72134752f * eta * eta) / Phi : -eta;
-                        hn = hh * __fmaf_rn(2.0f, zw, eta);
-                    }
-                }
-                const bool on = !(yy < gc.y);
-                const float tt = on ? yy * gc.x : 0.0f;   // dL/d(ln x)
+                const Term m = term(dx[x], a0r, a1, a1sq, wr);
+                const uint64_t on = __builtin_amdgcn_ballot_w64(m.yy > gc.y);
+                const uint64_t may = __builtin_amdgcn_ballot_w64(!(m.yy < gc.y * kMost));
+                cols |= on != may ? 1u << x : 0u;
+                add(q, m, __builtin_amdgcn_inverse_ballot_w64(on) ? m.yy * gc.x : 0.0f);
                 if (COUNT) {
-                    n.full += lane < m ? 1u : 0u;
-                    n.blend += on && lane < m ? 1u : 0u;
-                }
-                acc[9] += tt;
-                if constexpr (PLAIN) {
-                    const float T = tt * g.rq2;
-                    const float L = T * __fmaf_rn(d2, -2.0f / kLog2e, 1.0f);
-                    const float T0 = T * g.a0, La = L * g.a0;
-                    S0 += T;
-                    S1 += T0;
-                    SW = __fmaf_rn(T, g.w2, SW);
-                    acc[0] = __fmaf_rn(T0, g.a0, acc[0]);
-                    acc[3] = __fmaf_rn(T0, g.w2, acc[3]);
-                    L0 += L;
-                    L1 += La;
-                    LW = __fmaf_rn(L, g.w2, LW);
-                    acc[5] = __fmaf_rn(La, g.a0, acc[5]);
-                    acc[8] = __fmaf_rn(La, g.w2, acc[8]);
-                } else {
-                    // weights of p p^T (tw) and of the z terms (tz)
-                    const float D2 = EPAN ? d2 : d2 * (2.0f / kLog2e);
-                    const float p0 = g.a0 * g.rq, p1 = g.a1 * g.rq, p2 = g.w2 * g.rq;
-                    float tw = tt, tz = tt;
-                    if constexpr (EPAN) tz = tt != 0.0f ? tt * (3.0f * fast_rcp(1.0f - D2)) : 0.0f;
-                    if constexpr (NEAR) {
-                        tw = __fmaf_rn(tt, hn, tt);
-                        const float th = tt * hh;
-                        acc[13] = __fmaf_rn(th, p0, acc[13]);
-                        acc[14] = __fmaf_rn(th, p1, acc[14]);
-                        acc[15] = __fmaf_rn(th, p2, acc[15]);
-                    }
-                    const float kp = __fmaf_rn(tz, E - D2, tw), kq = __fmaf_rn(-tz, D2, tw);
-                    const float z0 = tz * p0, z1 = tz * p1, zh = tz * hp;
-                    acc[0] = __fmaf_rn(kp * p0, p0, acc[0]);
-                    acc[1] = __fmaf_rn(kp * p0, p1, acc[1]);
-                    acc[2] = __fmaf_rn(kq * p0, p2, acc[2]);
-                    acc[3] = __fmaf_rn(kp * p1, p1, acc[3]);
-                    acc[4] = __fmaf_rn(kq * p1, p2, acc[4]);
-                    acc[5] += __fmaf_rn(-tw, p2 * p2, __fmaf_rn(-zh, D2, tt));   // sum t - M_22
-                    acc[6] = __fmaf_rn(z0, p2, acc[6]);
-                    acc[7] = __fmaf_rn(z1, p2, acc[7]);
-                    acc[8] += zh;
+                    n.full += lane < cnt ? 1u : 0u;
+                    n.blend += m.yy > gc.y && lane < cnt ? 1u : 0u;
                 }
             }
-            if constexpr (PLAIN) {
-                acc[1] = __fmaf_rn(S1, a1, acc[1]);
-                acc[2] = __fmaf_rn(S0, a1sq, acc[2]);
-                acc[4] = __fmaf_rn(SW, a1, acc[4]);
-                acc[6] = __fmaf_rn(L1, a1, acc[6]);
-                acc[7] = __fmaf_rn(L0, a1sq, acc[7]);
-                acc[10] = __fmaf_rn(LW, a1, acc[10]);
-            }
+            tied |= (uint64_t)cols << (8 * y);
+            end_row(q, a1, a1sq);
+        }
+        // their pairs, left out above, as the forward decides them
+        while (__builtin_expect(tied != 0, 0)) {
+            const int e = __builtin_ctzll(tied), x = t.slot_x(k) + (e & 7), y = t.slot_y(k) + (e >> 3);
+            tied &= tied - 1;
+            const float dxx = ((float)x + 0.5f - h.x) - h.z, dy = ((float)y + 0.5f - h.y) - h.w;
+            const float a1 = r.z * dy, a1sq = a1 * a1;
+            const Term m = term(dxx, r.y * dy, a1, a1sq, __fmaf_rn(s.y, dy, 1.0f));
+            const float2 gc = st.pix[k][e];
+            const float yl = lframe_y<MODE>(gp[3], gp[4], gp[5], dxx, dy, t.unit(x, y), zn);
+            const bool on = !(m.yy < gc.y * kMost) && !(m.yy > gc.y) && !(yl < tau2);
+            Row q;
+            add(q, m, on ? m.yy * gc.x : 0.0f);
+            end_row(q, a1, a1sq);
+            if (COUNT) n.blend += on && lane < cnt ? 1u : 0u;
         }
         float out[NSLOT];
         if constexpr (PLAIN) {
@@ -549,13 +596,13 @@ __global__ __launch_bounds__(512) void xray_bwd_kernel(RenderParams rp, Buffers 
         lds_wave_sync();
         const int f = lane & 15;
         if (f < NSLOT) {
-            for (int at = lane >> 4; at < m; at += 4) {
+            for (int at = lane >> 4; at < cnt; at += 4) {
                 const float sum = st.acc[at * Wave::kAcc + f];
                 if (sum != 0.0f)
                     atomicAdd(reinterpret_cast<float *>(b.rgrad) + (size_t)st.item[at] * kGradFloats + f, sum);
             }
         }
-        if (COUNT) n.visits_full += lane == 0 ? (uint32_t)m : 0u;
+        if (COUNT) n.visits_full += lane == 0 ? (uint32_t)cnt : 0u;
     };
 
     Candidate cand;
