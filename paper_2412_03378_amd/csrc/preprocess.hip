@@ -814,7 +814,12 @@ __global__ __launch_bounds__(kGatherThreads) void gather_counts_kernel(
 // by binary search over the row prefixes and culls its rows to tile intervals (the
 // same intervals the preprocess counted); a scan of the interval lengths gives each
 // row its first instance.  The rows' lanes then write their tiles into LDS,
-// kEmitWindow instances at a time, from where they leave in order.
+// kEmitWindow instances at a time, from where they leave in order.  Rows longer than
+// kEmitWide tiles are written by the whole wave, straight to memory: a lane would write
+// its row alone, one tile after the other, while few of the other lanes have any in the
+// window (1920x1080, 64 frame-sized Gaussians in front of 200k small ones, rows of 240
+// tiles, scan and emission: 76.7 ms by the lanes, 3.0 by the wave, 6.2 by 256 threads
+// that searched the row of every instance; 4 frame-sized ones 4.71, 0.21 and 0.38).
 //
 // The kernel waits for a chain of loads per item (offset, item, its record) and
 // little else, so what counts is items in flight: a wave of its own per 64 items has
@@ -825,6 +830,7 @@ constexpr int kEmitThreads = 64;
 constexpr int kEmitRowsPerThread = 4;
 constexpr int kEmitRows = kEmitThreads * kEmitRowsPerThread;
 constexpr uint32_t kEmitWindow = 512;
+constexpr uint32_t kEmitWide = 32;
 // (12 views of 8k Gaussians, scan and emission: 35 us at 256 to 2048 waves, 39 at 4096,
 // 59 at 16384)
 constexpr int64_t kEmitWaves = 1024;
@@ -838,7 +844,7 @@ __global__ __launch_bounds__(kEmitThreads) void emit_kernel(RenderParams rp, Buf
     __shared__ int32_t s_toff[64], s_tx[64];
     __shared__ uint32_t s_rowbeg[65];              // first candidate row of each Gaussian
     __shared__ uint32_t s_tile[kEmitWindow];       // instances of the window: tile,
-    __shared__ uint8_t s_own[kEmitWindow];         // owning Gaussian (0..63)
+    __shared__ __align__(8) uint8_t s_own[kEmitWindow];   // owning Gaussian (0..63)
     __shared__ uint32_t s_gemit[64];               // instances found per Gaussian
     const int tid = threadIdx.x;
     const int items = 1 << lg;
@@ -920,13 +926,44 @@ __global__ __launch_bounds__(kEmitThreads) void emit_kernel(RenderParams rp, Buf
             if (tid >= d) inc += t;
         }
         const uint32_t run0 = done + inc - sum, chunk = __builtin_amdgcn_readlane(inc, 63);
-        for (uint32_t w0 = done; w0 < done + chunk; w0 += kEmitWindow) {   // uniform
+        // rows longer than kEmitWide: one after the other by the whole wave
+        bool any = false, narrow = false;   // such rows; others
+        {
+            uint32_t run = run0;
+#pragma unroll
+            for (int i = 0; i < kEmitRowsPerThread; ++i) {
+                uint64_t rows = __builtin_amdgcn_ballot_w64(cnt[i] > kEmitWide);
+                any = any || rows != 0;   // uniform
+                narrow = narrow || __builtin_amdgcn_ballot_w64(cnt[i] - 1u < kEmitWide) != 0;
+                const uint32_t item = rows != 0 ? s_item[own[i]] : 0u;
+                while (rows != 0) {
+                    const int l = __builtin_ctzll(rows);
+                    rows &= rows - 1;
+                    const uint32_t n = __builtin_amdgcn_readlane(cnt[i], l);
+                    const uint32_t first = __builtin_amdgcn_readlane(tile[i], l);
+                    const uint32_t who = __builtin_amdgcn_readlane(item, l);
+                    const int64_t at = (int64_t)base + (uint32_t)__builtin_amdgcn_readlane(run, l);
+                    for (uint32_t e = (uint32_t)tid; e < n; e += kEmitThreads) {
+                        if (at + e < capacity) {
+                            b.inst_key[at + e] = first + e;
+                            b.inst_val[at + e] = who;
+                        }
+                    }
+                }
+                run += cnt[i];
+            }
+        }
+        for (uint32_t w0 = done; narrow && w0 < done + chunk; w0 += kEmitWindow) {   // uniform
             const uint32_t wn = min(kEmitWindow, done + chunk - w0);
+            if (any) {   // uniform: the long rows' instances are nobody's here
+                reinterpret_cast<uint2 *>(s_own)[tid] = make_uint2(~0u, ~0u);
+                __syncthreads();
+            }
             uint32_t run = run0;
 #pragma unroll
             for (int i = 0; i < kEmitRowsPerThread; ++i) {
                 // instances run .. run + cnt of the row, cut to the window
-                const uint32_t e1 = min(run + cnt[i], w0 + wn);
+                const uint32_t e1 = cnt[i] > kEmitWide ? 0u : min(run + cnt[i], w0 + wn);
                 for (uint32_t e = max(run, w0); e < e1; ++e) {
                     s_tile[e - w0] = tile[i] + (e - run);
                     s_own[e - w0] = (uint8_t)own[i];
@@ -936,9 +973,10 @@ __global__ __launch_bounds__(kEmitThreads) void emit_kernel(RenderParams rp, Buf
             __syncthreads();
             for (uint32_t e = (uint32_t)tid; e < wn; e += kEmitThreads) {
                 const int64_t pos = (int64_t)base + w0 + e;
-                if (pos < capacity) {
+                const uint32_t who = s_own[e];
+                if (pos < capacity && who < 64u) {
                     b.inst_key[pos] = s_tile[e];
-                    b.inst_val[pos] = s_item[s_own[e]];
+                    b.inst_val[pos] = s_item[who];
                 }
             }
             __syncthreads();
