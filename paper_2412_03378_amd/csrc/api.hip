@@ -731,8 +731,14 @@ int enqueue_forward(vgr_ctx *c, const Prepared &p, const float *means, const flo
         // per-item counts in depth order with their block sums, then their
         // scan, whose total is the instance count (clamped to the capacity K)
         HIP_TRY(c, launch_gather_counts(b, mv, rp.total_tiles, ptr<uint32_t>(c->scan_tmp), s));
+        // (the emission waves' first items go to the sorts' scratch, free between them and
+        // larger: it has a sixteenth of the items' or instances' number of words)
+        uint32_t *starts = ptr<uint32_t>(c->sort_tmp);
+        const EmitSplit split = emit_split(mv, K);
+        if (c->sort_tmp.bytes < 4 * (size_t)split.waves)
+            return fail(c, VGR_ERR_HIP, "scratch of the emission");
         HIP_TRY(c, launch_count_scan(b.cnt_sorted, b.offsets, mv, ptr<uint32_t>(c->scan_tmp),
-                                     b.d_total, K, s));
+                                     b.d_total, K, starts, split, s));
         // an odd number of tile sort passes starts from the second pair of lists, to
         // end in the first
         const int tile_bits = bits_for(p.tiles);
@@ -741,7 +747,7 @@ int enqueue_forward(vgr_ctx *c, const Prepared &p, const float *means, const flo
             std::swap(be.inst_key, be.inst_key2);
             std::swap(be.inst_val, be.inst_val2);
         }
-        HIP_TRY(c, launch_emit(rp, be, mv, K, s));
+        HIP_TRY(c, launch_emit(rp, be, mv, split, starts, s));
         mark_end(c, ST_SCAN_EMIT);
         mark(c, ST_SORT_TILES);
         if (rp.tile_resort) {

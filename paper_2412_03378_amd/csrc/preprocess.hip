@@ -807,36 +807,36 @@ __global__ __launch_bounds__(kGatherThreads) void gather_counts_kernel(
     }
 }
 
-// Emission of the (tile, Gaussian) pairs in the items' order.  Each wave owns
-// 2^lg consecutive items, whose instance ranges are contiguous.  Their candidate
-// tile rows (the rows of each rectangle, in item then row order) are processed
-// 256 at a time, four consecutive rows per lane: each lane finds the owning item
-// by binary search over the row prefixes and culls its rows to tile intervals (the
-// same intervals the preprocess counted); a scan of the interval lengths gives each
-// row its first instance.  The rows' lanes then write their tiles into LDS,
-// kEmitWindow instances at a time, from where they leave in order.  Rows longer than
-// kEmitWide tiles are written by the whole wave, straight to memory: a lane would write
-// its row alone, one tile after the other, while few of the other lanes have any in the
-// window (1920x1080, 64 frame-sized Gaussians in front of 200k small ones, rows of 240
-// tiles, scan and emission: 76.7 ms by the lanes, 3.0 by the wave, 6.2 by 256 threads
-// that searched the row of every instance; 4 frame-sized ones 4.71, 0.21 and 0.38).
+// Emission of the (tile, Gaussian) pairs in the items' order.  A wave takes a group of
+// 2^lg_items consecutive items, or of a group with many instances the part that lies
+// between two multiples of 2^lg (starts[wave] names its first item: launch_count_scan).
+// The items' candidate tile rows (the rows of each rectangle, in item then row order)
+// are processed 256 at a time, four consecutive rows per lane: each lane finds the
+// owning item by binary search over the row prefixes and culls its rows to tile
+// intervals (the same intervals the preprocess counted); a scan of the interval lengths
+// gives each row its first instance.  The rows' lanes then write their tiles into LDS,
+// kEmitWindow instances at a time, from where they leave in order; rows longer than
+// kEmitWide tiles are written by the whole wave, straight to memory.
 //
 // The kernel waits for a chain of loads per item (offset, item, its record) and
 // little else, so what counts is items in flight: a wave of its own per 64 items has
 // four times as many as 256 threads per 64 items did (168 -> 113 us for 1.5M items,
 // 15.8M instances; windows of 256 and 1024 the same; writing through a search of the
-// rows for every instance instead of the window, 3 % slower).
+// rows for every instance instead of the window, 3 % slower).  Groups are cut by their
+// instances because large Gaussians sit side by side in depth order: with 64 items a
+// wave and a lane a row, 64 frame-sized ones (rows of 240 tiles) in front of 200k small
+// ones at 1920x1080 took 76.7 ms for the scan and the emission, 2000 of 60 tiles across
+// 1.58 ms; with 256 threads per 64 items and a search of the rows for every instance
+// 6.2 and 0.33 ms; now 0.060 and 0.064 ms.
 constexpr int kEmitThreads = 64;
 constexpr int kEmitRowsPerThread = 4;
 constexpr int kEmitRows = kEmitThreads * kEmitRowsPerThread;
 constexpr uint32_t kEmitWindow = 512;
 constexpr uint32_t kEmitWide = 32;
-// (12 views of 8k Gaussians, scan and emission: 35 us at 256 to 2048 waves, 39 at 4096,
-// 59 at 16384)
-constexpr int64_t kEmitWaves = 1024;
 
 __global__ __launch_bounds__(kEmitThreads) void emit_kernel(RenderParams rp, Buffers b, int64_t m,
-                                                            int64_t capacity, int lg)
+                                                            const uint32_t *__restrict__ starts,
+                                                            EmitSplit split)
 {
     __shared__ uint32_t s_item[64];
     __shared__ ushort4 s_rect[64];
@@ -847,18 +847,32 @@ __global__ __launch_bounds__(kEmitThreads) void emit_kernel(RenderParams rp, Buf
     __shared__ __align__(8) uint8_t s_own[kEmitWindow];   // owning Gaussian (0..63)
     __shared__ uint32_t s_gemit[64];               // instances found per Gaussian
     const int tid = threadIdx.x;
-    const int items = 1 << lg;
-    const int64_t j0 = (int64_t)blockIdx.x << lg;
-    // items past those with instances (they sort last) emit nothing (uniform)
-    if (j0 >= (int64_t)b.d_total[6]) return;
-    const uint32_t base = b.offsets[j0];
-    {   // the wave's Gaussians and their candidate row counts
-        const int64_t j = j0 + tid;
+    const uint32_t K = b.d_total[0];
+    // (a capture's grid covers its capacity; items past those with instances sort last)
+    if (blockIdx.x >= split.groups + (K >> split.lg)) return;   // uniform
+    const uint32_t j0 = starts[blockIdx.x], group = j0 >> split.lg_items;
+    if (j0 >= b.d_total[6]) return;   // uniform
+    const uint64_t cut = (uint64_t)(blockIdx.x - group) << split.lg;
+    // the wave's instances [first, last) of the items from j0 on
+    const uint32_t last = (uint32_t)min(cut + (1u << split.lg), (uint64_t)K);
+    const int64_t j = (int64_t)j0 + tid;
+    const bool mine = j < m && (uint32_t)(j >> split.lg_items) == group;
+    const uint32_t beg = mine ? b.offsets[j] : last, end = mine ? b.offsets[j + 1] : last;
+    const uint32_t base = __builtin_amdgcn_readfirstlane(beg);
+    const uint32_t first = max((uint32_t)cut, base);
+    if (first >= last) return;   // uniform
+    const uint32_t lo = first - base, hi = last - base;
+    uint32_t want = 0;   // instances, if the item's first one is this wave's
+    int nitems;
+    {
+        // the Gaussians and their candidate row counts
         CullRows cr = { 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f };
         ushort4 rect = make_ushort4(0, 0, 0, 0);
         uint32_t item = 0, rows = 0;
         int32_t toff = 0, txs = 0;
-        if (tid < items && j < m && b.offsets[j + 1] > b.offsets[j]) {   // with instances
+        const bool on = beg < last && beg < end;
+        nitems = __builtin_popcountll(__builtin_amdgcn_ballot_w64(on));
+        if (on) {
             item = b.item_ids[j];
             rect = b.rect[item];
             const float4 c6 = b.geom[(size_t)item * kRecVec + 6];
@@ -868,6 +882,7 @@ __global__ __launch_bounds__(kEmitThreads) void emit_kernel(RenderParams rp, Buf
             toff = vi.tile_off;
             txs = vi.tiles_x;
             rows = (uint32_t)rect.w - (uint32_t)rect.y + 1u;
+            want = beg >= cut ? end - beg : 0u;
         }
         s_item[tid] = item;
         s_gemit[tid] = 0u;
@@ -899,23 +914,22 @@ __global__ __launch_bounds__(kEmitThreads) void emit_kernel(RenderParams rp, Buf
             own[i] = 0;
             if (rl < cn) {
                 const uint32_t r = c0 + rl;
-                // largest g with s_rowbeg[g] <= r: Gaussians without rows share
-                // their prefix with the next one, which the search prefers
-                int lo = 0, hi = items - 1;
-                while (lo < hi) {
-                    const int mid = (lo + hi + 1) >> 1;
-                    if (s_rowbeg[mid] <= r) lo = mid;
-                    else hi = mid - 1;
+                // largest g with s_rowbeg[g] <= r
+                int g0 = 0, g1 = nitems - 1;
+                while (g0 < g1) {
+                    const int mid = (g0 + g1 + 1) >> 1;
+                    if (s_rowbeg[mid] <= r) g0 = mid;
+                    else g1 = mid - 1;
                 }
-                const ushort4 rect = s_rect[lo];
-                const int row = (int)rect.y + (int)(r - s_rowbeg[lo]);
+                const ushort4 rect = s_rect[g0];
+                const int row = (int)rect.y + (int)(r - s_rowbeg[g0]);
                 int t0 = 0, t1 = -1;
-                if (cull_row(s_cull[lo], row, rp.tile_w, rp.tile_h, rect.x, rect.z, t0, t1)) {
+                if (cull_row(s_cull[g0], row, rp.tile_w, rp.tile_h, rect.x, rect.z, t0, t1)) {
                     cnt[i] = (uint32_t)(t1 - t0 + 1);
-                    atomicAdd(&s_gemit[lo], cnt[i]);
+                    atomicAdd(&s_gemit[g0], cnt[i]);
                 }
-                tile[i] = (uint32_t)(s_toff[lo] + row * s_tx[lo] + t0);
-                own[i] = lo;
+                tile[i] = (uint32_t)(s_toff[g0] + row * s_tx[g0] + t0);
+                own[i] = g0;
             }
             sum += cnt[i];
         }
@@ -926,36 +940,37 @@ __global__ __launch_bounds__(kEmitThreads) void emit_kernel(RenderParams rp, Buf
             if (tid >= d) inc += t;
         }
         const uint32_t run0 = done + inc - sum, chunk = __builtin_amdgcn_readlane(inc, 63);
-        // rows longer than kEmitWide: one after the other by the whole wave
-        bool any = false, narrow = false;   // such rows; others
+        // the chunk's instances that are the wave's (uniform)
+        const uint32_t e0 = max(done, lo), e1 = min(done + chunk, hi);
+        done += chunk;
+        if (e0 >= e1) continue;   // uniform
+        bool wide = false, narrow = false;   // rows longer than kEmitWide; others
         {
             uint32_t run = run0;
 #pragma unroll
             for (int i = 0; i < kEmitRowsPerThread; ++i) {
                 uint64_t rows = __builtin_amdgcn_ballot_w64(cnt[i] > kEmitWide);
-                any = any || rows != 0;   // uniform
+                wide = wide || rows != 0;   // uniform
                 narrow = narrow || __builtin_amdgcn_ballot_w64(cnt[i] - 1u < kEmitWide) != 0;
                 const uint32_t item = rows != 0 ? s_item[own[i]] : 0u;
                 while (rows != 0) {
                     const int l = __builtin_ctzll(rows);
                     rows &= rows - 1;
-                    const uint32_t n = __builtin_amdgcn_readlane(cnt[i], l);
-                    const uint32_t first = __builtin_amdgcn_readlane(tile[i], l);
+                    const uint32_t r0 = __builtin_amdgcn_readlane(run, l);
+                    const uint32_t r1 = r0 + __builtin_amdgcn_readlane(cnt[i], l);
+                    const uint32_t t0 = __builtin_amdgcn_readlane(tile[i], l);
                     const uint32_t who = __builtin_amdgcn_readlane(item, l);
-                    const int64_t at = (int64_t)base + (uint32_t)__builtin_amdgcn_readlane(run, l);
-                    for (uint32_t e = (uint32_t)tid; e < n; e += kEmitThreads) {
-                        if (at + e < capacity) {
-                            b.inst_key[at + e] = first + e;
-                            b.inst_val[at + e] = who;
-                        }
+                    for (uint32_t e = max(r0, e0) + (uint32_t)tid; e < min(r1, e1); e += kEmitThreads) {
+                        b.inst_key[(size_t)base + e] = t0 + (e - r0);
+                        b.inst_val[(size_t)base + e] = who;
                     }
                 }
                 run += cnt[i];
             }
         }
-        for (uint32_t w0 = done; narrow && w0 < done + chunk; w0 += kEmitWindow) {   // uniform
-            const uint32_t wn = min(kEmitWindow, done + chunk - w0);
-            if (any) {   // uniform: the long rows' instances are nobody's here
+        for (uint32_t w0 = e0; narrow && w0 < e1; w0 += kEmitWindow) {   // uniform
+            const uint32_t wn = min(kEmitWindow, e1 - w0);
+            if (wide) {   // uniform: the long rows' instances are nobody's here
                 reinterpret_cast<uint2 *>(s_own)[tid] = make_uint2(~0u, ~0u);
                 __syncthreads();
             }
@@ -963,8 +978,8 @@ __global__ __launch_bounds__(kEmitThreads) void emit_kernel(RenderParams rp, Buf
 #pragma unroll
             for (int i = 0; i < kEmitRowsPerThread; ++i) {
                 // instances run .. run + cnt of the row, cut to the window
-                const uint32_t e1 = cnt[i] > kEmitWide ? 0u : min(run + cnt[i], w0 + wn);
-                for (uint32_t e = max(run, w0); e < e1; ++e) {
+                const uint32_t re = cnt[i] > kEmitWide ? 0u : min(run + cnt[i], w0 + wn);
+                for (uint32_t e = max(run, w0); e < re; ++e) {
                     s_tile[e - w0] = tile[i] + (e - run);
                     s_own[e - w0] = (uint8_t)own[i];
                 }
@@ -972,22 +987,20 @@ __global__ __launch_bounds__(kEmitThreads) void emit_kernel(RenderParams rp, Buf
             }
             __syncthreads();
             for (uint32_t e = (uint32_t)tid; e < wn; e += kEmitThreads) {
-                const int64_t pos = (int64_t)base + w0 + e;
+                const size_t pos = (size_t)base + w0 + e;
                 const uint32_t who = s_own[e];
-                if (pos < capacity && who < 64u) {
+                if (who < 64u) {
                     b.inst_key[pos] = s_tile[e];
                     b.inst_val[pos] = s_item[who];
                 }
             }
             __syncthreads();
         }
-        done += chunk;
     }
     // every Gaussian must have produced exactly the tile count the preprocess
     // gave it (which sized the lists): count the items that did not
-    const int64_t j = j0 + tid;
-    const uint32_t want = tid < items && j < m ? b.offsets[j + 1] - b.offsets[j] : 0u;
-    const uint64_t bad = __builtin_amdgcn_ballot_w64(s_gemit[tid] != want);
+    __syncthreads();
+    const uint64_t bad = __builtin_amdgcn_ballot_w64(want != 0 && s_gemit[tid] != want);
     if (tid == 0 && bad != 0) atomicAdd(&b.d_total[7], (uint32_t)__builtin_popcountll(bad));
 }
 
@@ -1626,13 +1639,33 @@ hipError_t launch_gather_counts(const Buffers &b, int64_t m, int32_t total_tiles
     return hipGetLastError();
 }
 
-hipError_t launch_emit(const RenderParams &rp, const Buffers &b, int64_t m, int64_t capacity,
-                       hipStream_t s)
+// Items per wave: 64 where that brings 4096 waves, else 32, fewer (down to 4) in calls
+// with less than 1024 waves; cut at 2048 instances, at fewer (down to 128) in calls with
+// less than 1024 waves.
+// Emission in us by 64, 32 and 16 items a wave: 50k items 11, 11, 12, 100k 19, 14, 18,
+// 200k 22, 22, 27, 400k 30, 33, 46.  (12 views of 8k Gaussians, scan and emission: 35
+// at 256 to 2048 waves, 39 at 4096, 59 at 16384.)  Cuts at 2048, 4096 and 8192 instances,
+// scan and emission: 3M Gaussians at 1600x1064 169, 168, 167, 2000 of 15 tiles across in
+// front of 200k small ones 46, 63, 83.  Waves of equal numbers of instances instead of
+// groups, on average those of 64 items: the 3M 193, since parts of items at both ends and
+// a power of two leave a third of the lanes without an item.
+EmitSplit emit_split(int64_t items, int64_t instances)
 {
-    // 64 items per wave, fewer (down to 4) in calls with less than kEmitWaves waves
-    int lg = 6;
-    while (lg > 2 && (m >> lg) < kEmitWaves) --lg;
-    emit_kernel<<<grid_for(m, 1 << lg), kEmitThreads, 0, s>>>(rp, b, m, capacity, lg);
+    EmitSplit e;
+    e.lg_items = items >> 6 >= 4096 ? 6 : 5;
+    while (e.lg_items > 2 && (items >> e.lg_items) < 1024) --e.lg_items;
+    e.groups = (uint32_t)((items + (1 << e.lg_items) - 1) >> e.lg_items);
+    e.lg = 11;
+    while (e.lg > 7 && (int64_t)e.groups + (instances >> e.lg) < 1024) --e.lg;
+    e.waves = e.groups + (uint32_t)(instances >> e.lg);
+    return e;
+}
+
+hipError_t launch_emit(const RenderParams &rp, const Buffers &b, int64_t m, const EmitSplit &split,
+                       const uint32_t *starts, hipStream_t s)
+{
+    if (split.waves == 0) return hipSuccess;
+    emit_kernel<<<split.waves, kEmitThreads, 0, s>>>(rp, b, m, starts, split);
     return hipGetLastError();
 }
 

@@ -78,10 +78,13 @@ __global__ __launch_bounds__(kScanThreads) void scan_partials_kernel(uint32_t *_
     }
 }
 
+// Also the first item of each wave of the emission (EmitSplit).
 __global__ __launch_bounds__(kThreads) void scan_down_kernel(const uint32_t *__restrict__ in,
                                                              uint32_t *__restrict__ out,
                                                              int64_t n,
-                                                             const uint32_t *__restrict__ partial)
+                                                             const uint32_t *__restrict__ partial,
+                                                             uint32_t *__restrict__ starts,
+                                                             EmitSplit split)
 {
     __shared__ uint32_t tile[kTile];
     const int64_t base = (int64_t)blockIdx.x * kTile;
@@ -110,6 +113,32 @@ __global__ __launch_bounds__(kThreads) void scan_down_kernel(const uint32_t *__r
     for (int i = 0; i < kItems; ++i) {
         int64_t idx = base + (int64_t)i * kThreads + threadIdx.x;
         if (idx < n) out[idx] = tile[i * kThreads + threadIdx.x];
+    }
+    // A wave of the emission begins with its group's first item, or with the item that
+    // holds the instance at its cut; a cut at the group's end names the last item.
+    // (Short loops: unrolled ones cost more in instruction fetches than they save.)
+    auto put = [&](uint32_t i, uint32_t cut) {
+        const uint32_t w = (uint32_t)((base + i) >> split.lg_items) + cut;
+        if (w < split.waves) starts[w] = (uint32_t)base + i;
+    };
+    const uint32_t b0 = tile[0], b1 = b0 + total;
+    const uint32_t nb = (uint32_t)min((int64_t)kTile, n - base);
+    const uint32_t cmask = (1u << split.lg) - 1u;
+    for (uint32_t i0 = threadIdx.x << split.lg_items; i0 < nb; i0 += kThreads << split.lg_items) {
+        const uint32_t i1 = min(i0 + (1u << split.lg_items), nb);
+        const uint32_t end = i1 < (uint32_t)kTile ? tile[i1] : b1;
+        put(i0, tile[i0] >> split.lg);
+        if ((end & cmask) == 0) put(i1 - 1u, end >> split.lg);
+    }
+    for (uint64_t x = (((uint64_t)b0 + cmask) >> split.lg) + threadIdx.x; x << split.lg < b1; x += kThreads) {
+        // the last item that does not start behind the cut
+        uint32_t lo = 0, hi = nb - 1u;
+        while (lo < hi) {
+            const uint32_t mid = (lo + hi + 1u) >> 1;
+            if (tile[mid] <= x << split.lg) lo = mid;
+            else hi = mid - 1u;
+        }
+        put(lo, (uint32_t)x);
     }
 }
 
@@ -399,13 +428,15 @@ int64_t scan_tmp_words(int64_t n)
 }
 
 hipError_t launch_count_scan(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *tmp,
-                             uint32_t *d_total, int64_t capacity, hipStream_t s)
+                             uint32_t *d_total, int64_t capacity, uint32_t *starts,
+                             const EmitSplit &split, hipStream_t s)
 {
     const int64_t ng = n > 0 ? (n + kScanGrain - 1) / kScanGrain : 0;
     scan_partials_kernel<<<1, kScanThreads, 0, s>>>(tmp, ng, out + (n > 0 ? n : 0), d_total,
                                                 capacity);
     if (n > 0)
-        scan_down_kernel<<<dim3((unsigned)blocks_for(n)), dim3(kThreads), 0, s>>>(in, out, n, tmp);
+        scan_down_kernel<<<dim3((unsigned)blocks_for(n)), dim3(kThreads), 0, s>>>(in, out, n, tmp,
+                                                                                 starts, split);
     return hipGetLastError();
 }
 

@@ -272,8 +272,17 @@ hipError_t launch_compact_items(const RenderParams &rp, const Buffers &b, hipStr
 // per-tile ranges and the tile-order counters.
 hipError_t launch_gather_counts(const Buffers &b, int64_t m, int32_t total_tiles,
                                 uint32_t *partial, hipStream_t s);
-hipError_t launch_emit(const RenderParams &rp, const Buffers &b, int64_t m, int64_t capacity,
-                       hipStream_t s);
+// Emission of the items' instances: the items in `groups` of 2^lg_items, a group's
+// instances cut at the multiples of 2^lg.  Wave group + k takes the instances of the
+// group from k 2^lg on, k = (first instance >> lg) .. (end >> lg), the last perhaps none.
+struct EmitSplit {
+    uint32_t groups, waves;
+    int lg_items, lg;
+};
+EmitSplit emit_split(int64_t items, int64_t instances);
+// starts: the waves' first items, from launch_count_scan.
+hipError_t launch_emit(const RenderParams &rp, const Buffers &b, int64_t m, const EmitSplit &split,
+                       const uint32_t *starts, hipStream_t s);
 // clear: zero the ranges first (done by launch_gather_counts when it ran).
 hipError_t launch_ranges(const Buffers &b, int64_t capacity_bound, int32_t total_tiles,
                          bool clear, hipStream_t s);
@@ -323,8 +332,10 @@ hipError_t launch_preprocess_bwd(const RenderParams &rp, const Buffers &b, const
 // d_total[0], [1], [5]; d_total[7] = 0.  tmp: scan_tmp_words(n) u32.
 constexpr int64_t kScanGrain = 256;
 int64_t scan_tmp_words(int64_t n);
+// starts: the first item of each wave of the emission (split.waves words).
 hipError_t launch_count_scan(const uint32_t *in, uint32_t *out, int64_t n, uint32_t *tmp,
-                             uint32_t *d_total, int64_t capacity, hipStream_t s);
+                             uint32_t *d_total, int64_t capacity, uint32_t *starts,
+                             const EmitSplit &split, hipStream_t s);
 
 // Radix sort of (key, val) u32 pairs; element count read from *d_n on the
 // device, grids sized for n_bound.  Ping-pong buffers keys/vals <-> keys2/vals2;

@@ -1,9 +1,8 @@
-"""Emission of long tile rows, written by the whole wave, beside short ones: rows
-around the length at which that begins, rows longer than the window of the
-instances, and both kinds under one wave's items.  The image against the oracle
-on sampled pixels with the suite's bounds; every item has to emit the tiles that
-the preprocess counted, and the tile lists have to hold each item once (the
-image of a list in any other order or with a repeated entry differs)."""
+"""Emission by waves that own instances: items that reach into several waves' shares,
+several items per wave, and more than 64; long tile rows, written by the whole
+wave, beside short ones, around the length at which that begins and longer than
+the window of the instances.  The image against the oracle on sampled pixels with
+the suite's bounds; every item has to emit the tiles that the preprocess counted."""
 import numpy as np
 import pytest
 
