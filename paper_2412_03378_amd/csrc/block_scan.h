@@ -8,6 +8,9 @@ namespace vgr {
 namespace {
 
 constexpr int kScanThreads = 1024;
+// Longest array that 256 threads scan: one round.  (3k words by 256 and 1024 threads 4.4
+// and 5.0 us, 200 words 2.1 and 4.7.)
+constexpr int64_t kScanShort = 16 * 256;
 
 // Exclusive scan, in place, of c[0..n) (16-byte aligned) by the T threads of the block;
 // returns the total.  A serial chain of rounds, so a round takes 16 T words, four loads
@@ -23,8 +26,11 @@ __device__ __forceinline__ uint32_t scan_in_place(uint32_t *__restrict__ c, int6
     for (int64_t base = 0; base < n; base += Q * 4 * T) {   // uniform
         uint4 v[Q];
         uint32_t inc[Q];
+        // quarters of the round that hold words (uniform): a short array fills one
+        const int nq = (int)min((int64_t)Q, (n - base + 4 * T - 1) / (4 * T));
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
+            if (q >= nq) break;
             const int64_t k = base + 4 * ((int64_t)q * T + threadIdx.x);
             if (k + 3 < n) {
                 v[q] = *reinterpret_cast<const uint4 *>(c + k);
@@ -37,6 +43,7 @@ __device__ __forceinline__ uint32_t scan_in_place(uint32_t *__restrict__ c, int6
         }
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
+            if (q >= nq) break;
             inc[q] = v[q].x + v[q].y + v[q].z + v[q].w;
 #pragma unroll
             for (int d = 1; d < 64; d <<= 1) {
@@ -48,6 +55,7 @@ __device__ __forceinline__ uint32_t scan_in_place(uint32_t *__restrict__ c, int6
         __syncthreads();
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
+            if (q >= nq) break;
             uint32_t off = carry;
 #pragma unroll
             for (int i = 0; i < W; ++i) {

@@ -720,15 +720,15 @@ __device__ __forceinline__ uint32_t emit_block_scan(uint32_t v, uint32_t *wsum, 
 // takes) into d_total[6].
 // (187k counts: 207 -> 46 us; 256 threads with 16 separate counts each went through
 // four times the rounds, and 1024 such threads thrashed the L1.)
-__global__ __launch_bounds__(kScanThreads) void count_total_kernel(uint32_t *__restrict__ parts,
-                                                                    int64_t nb, int64_t nc,
-                                                                    uint32_t *__restrict__ d_total,
-                                                                    uint32_t *__restrict__ h_total)
+template <int T>
+__global__ __launch_bounds__(T) void count_total_kernel(uint32_t *__restrict__ parts, int64_t nb,
+                                                        int64_t nc, uint32_t *__restrict__ d_total,
+                                                        uint32_t *__restrict__ h_total)
 {
-    __shared__ uint32_t s_part[kScanThreads / 64];
+    __shared__ uint32_t s_part[T / 64];
     if (blockIdx.x == 0) {
         uint32_t acc = 0;
-        for (int64_t k = threadIdx.x; k < nb; k += kScanThreads) acc += parts[nc + k];
+        for (int64_t k = threadIdx.x; k < nb; k += T) acc += parts[nc + k];
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
         if ((threadIdx.x & 63) == 0) s_part[threadIdx.x >> 6] = acc;
@@ -736,13 +736,13 @@ __global__ __launch_bounds__(kScanThreads) void count_total_kernel(uint32_t *__r
         if (threadIdx.x == 0) {
             uint32_t K = 0;
 #pragma unroll
-            for (int w = 0; w < kScanThreads / 64; ++w) K += s_part[w];
+            for (int w = 0; w < T / 64; ++w) K += s_part[w];
             d_total[4] = K;
             if (h_total) h_total[0] = K;
         }
         return;
     }
-    const uint32_t items = scan_in_place(parts, nc);
+    const uint32_t items = scan_in_place<T>(parts, nc);
     if (threadIdx.x == 0) {
         d_total[6] = items;
         if (h_total) h_total[2] = items;
@@ -1607,8 +1607,12 @@ hipError_t launch_preprocess(const RenderParams &rp, const Buffers &b, const flo
 #undef VGR_PRE
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    count_total_kernel<<<2, kScanThreads, 0, s>>>(b.blk_counts, (int64_t)grid.x * grid.y,
-                                         (int64_t)grid.x * rp.n_views, b.d_total, b.h_total);
+    const int64_t nb = (int64_t)grid.x * grid.y, nc = (int64_t)grid.x * rp.n_views;
+    if (nc <= kScanShort)
+        count_total_kernel<256><<<2, 256, 0, s>>>(b.blk_counts, nb, nc, b.d_total, b.h_total);
+    else
+        count_total_kernel<kScanThreads><<<2, kScanThreads, 0, s>>>(b.blk_counts, nb, nc, b.d_total,
+                                                                    b.h_total);
     return hipGetLastError();
 }
 

@@ -61,13 +61,13 @@ __device__ inline uint32_t block_exclusive_scan(uint32_t v, uint32_t *total)
 // With d_total, the total is also the instance count K: d_total[0] = K
 // clamped to capacity, d_total[1] = overflow, d_total[5] set (sticky) on
 // overflow, d_total[7] = 0 (the emission's mismatch counter).
-__global__ __launch_bounds__(kScanThreads) void scan_partials_kernel(uint32_t *__restrict__ partial,
-                                                                      int64_t nb,
-                                                                      uint32_t *__restrict__ total_out,
-                                                                      uint32_t *__restrict__ d_total,
-                                                                      int64_t capacity)
+template <int T>
+__global__ __launch_bounds__(T) void scan_partials_kernel(uint32_t *__restrict__ partial, int64_t nb,
+                                                          uint32_t *__restrict__ total_out,
+                                                          uint32_t *__restrict__ d_total,
+                                                          int64_t capacity)
 {
-    const uint32_t total = scan_in_place(partial, nb);
+    const uint32_t total = scan_in_place<T>(partial, nb);
     if (threadIdx.x == 0 && total_out) *total_out = total;
     if (threadIdx.x == 0 && d_total) {
         const bool over = (int64_t)total > capacity;
@@ -432,8 +432,13 @@ hipError_t launch_count_scan(const uint32_t *in, uint32_t *out, int64_t n, uint3
                              const EmitSplit &split, hipStream_t s)
 {
     const int64_t ng = n > 0 ? (n + kScanGrain - 1) / kScanGrain : 0;
-    scan_partials_kernel<<<1, kScanThreads, 0, s>>>(tmp, ng, out + (n > 0 ? n : 0), d_total,
-                                                capacity);
+    // (one round of 256 threads, else many threads)
+    if (ng <= kScanShort)
+        scan_partials_kernel<kThreads><<<1, kThreads, 0, s>>>(tmp, ng, out + (n > 0 ? n : 0), d_total,
+                                                              capacity);
+    else
+        scan_partials_kernel<kScanThreads><<<1, kScanThreads, 0, s>>>(tmp, ng, out + n, d_total,
+                                                                      capacity);
     if (n > 0)
         scan_down_kernel<<<dim3((unsigned)blocks_for(n)), dim3(kThreads), 0, s>>>(in, out, n, tmp,
                                                                                  starts, split);
