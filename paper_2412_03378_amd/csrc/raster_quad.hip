@@ -732,12 +732,8 @@ __device__ __forceinline__ void blocks_bwd(const RenderParams &rp, const Buffers
                     const float hp = __fmaf_rn(p0, p0, p1 * p1);
                     const float E = rs.w, D2 = E * hp;
                     float ex;
-                    if constexpr (EPAN) {
-                        const float h2 = fmaxf(1.0f - D2, 0.0f);
-                        ex = h2 * __builtin_amdgcn_sqrtf(h2);
-                    } else {
-                        ex = fast_exp2(-(0.5f * kLog2e) * D2);
-                    }
+                    if constexpr (EPAN) ex = epan_ray(D2);
+                    else ex = fast_exp2(-(0.5f * kLog2e) * D2);
                     float y = (NEAR ? fabsf(rs.z) : rs.z) * un * rq * ex;
                     // near-plane segment: y *= Phi(eta); hn = h (eta + 2 zn |w|) and
                     // h = phi(eta) / Phi(eta) enter the moments below

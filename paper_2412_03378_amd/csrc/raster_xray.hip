@@ -313,12 +313,8 @@ __global__ __launch_bounds__(512) void xray_fwd_kernel(RenderParams rp, Buffers 
                                            __fmaf_rn(c.s.y, dy[iy], wc[ix]));
                 const float d2 = c.s.w * (g.h * g.rq2);   // (log2 e / 2) D^2, or D^2 (EPAN)
                 float ex;
-                if constexpr (EPAN) {
-                    const float h2 = fmaxf(1.0f - d2, 0.0f);
-                    ex = h2 * __builtin_amdgcn_sqrtf(h2);
-                } else {
-                    ex = fast_exp2(-d2);
-                }
+                if constexpr (EPAN) ex = epan_ray(d2);
+                else ex = fast_exp2(-d2);
                 float y = (NEAR ? fabsf(c.s.z) : c.s.z) * (g.rq * ex);
                 if constexpr (NEAR) {
                     if (c.s.z < 0.0f) {   // uniform
@@ -456,12 +452,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(5))) void x
             m.hp = m.g.h * m.g.rq2;
             m.d2 = s.w * m.hp;   // (log2 e / 2) D^2, or D^2 (EPAN)
             float ex;
-            if constexpr (EPAN) {
-                const float h2 = fmaxf(1.0f - m.d2, 0.0f);
-                ex = h2 * __builtin_amdgcn_sqrtf(h2);
-            } else {
-                ex = fast_exp2(-m.d2);
-            }
+            if constexpr (EPAN) ex = epan_ray(m.d2);
+            else ex = fast_exp2(-m.d2);
             m.yy = (NEAR ? fabsf(s.z) : s.z) * (m.g.rq * ex);
             m.hh = m.hn = 0.0f;
             if constexpr (NEAR) {
