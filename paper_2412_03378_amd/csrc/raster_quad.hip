@@ -721,7 +721,8 @@ __device__ __forceinline__ void blocks_bwd(const RenderParams &rp, const Buffers
                     // this wave alone writes them)
                     const uint32_t sum_at = BPW == 4 ? (off >> 4) * kAcc + max(e, 0) : 0;
                     const float sum = BPW == 4 ? st.acc[sum_at] : 0.0f;
-                    const bool bl = ((bmask >> (off >> 4)) & 1u) != 0 && off != kPad;
+                    const uint32_t en = (off >> 4) & 63u;   // (the pad: any)
+                    const bool bl = off != kPad && ((bmask >> en) & 1u) != 0;
                     const float dx = (pxk - h.x) - h.z, dy = (pyk - h.y) - h.w;
                     const float a0 = __fmaf_rn(rr.y, dy, rr.x * dx);
                     const float a1 = __fmaf_rn(rr.w, dy, rr.z * dx);
@@ -755,7 +756,7 @@ __device__ __forceinline__ void blocks_bwd(const RenderParams &rp, const Buffers
                     bool clamped = false;
                     float ye = y;
                     if constexpr (CLAMP) {
-                        clamped = bl && ((cm >> (off >> 4)) & 1u) != 0;
+                        clamped = bl && ((cm >> en) & 1u) != 0;
                         ye = clamped ? ymax : y;
                     }
                     const float om = fast_exp2(-ye);
