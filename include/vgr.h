@@ -381,8 +381,9 @@ int vgr_graph_check(vgr_ctx *ctx, int64_t *instances);
 /* Time the step (forward, plus backward when dL_dout is not NULL) for each
  * launch shape: tile 8x8, 16x8, 16x16, 32x8 with 64-record batches, then the
  * same tiles with 32-record batches (candidates 0..7), with HIP events over
- * `iters` calls after one warm-up call.  The fastest becomes the context's
- * shape for calls of the same workload class that leave tile_w = tile_h = 0
+ * `iters` calls after one warm-up call.  Only the splatting opacity has a
+ * 32-record form: elsewhere candidates 4..7 are 0..3 and take their times.
+ * The fastest becomes the context's shape for calls of the same workload class that leave tile_w = tile_h = 0
  * or batch = 0 (the class: total pixels and Gaussians in powers of two, mode,
  * alpha_model, kernel, tile_resort, near_segment), and its last tuned shape
  * for other classes.  Reports it in *best_tile_w, *best_tile_h, *best_batch

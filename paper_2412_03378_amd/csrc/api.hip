@@ -1220,6 +1220,9 @@ int vgr_autotune(vgr_ctx *c, const vgr_settings *st, int64_t n, const float *mea
     static const int cand[VGR_TUNE_CANDIDATES][3] = {
         { 8, 8, 64 }, { 16, 8, 64 }, { 16, 16, 64 }, { 32, 8, 64 },
         { 8, 8, 32 }, { 16, 8, 32 }, { 16, 16, 32 }, { 32, 8, 32 } };
+    // only the splatting opacity's rasterisers have a 32-record form: elsewhere the last
+    // four candidates are the first four, and are not run
+    const int distinct = st->alpha_model == VGR_ALPHA_SPLAT ? VGR_TUNE_CANDIDATES : 4;
     if (iters < 1) iters = 3;
     hipEvent_t e0, e1;
     HIP_TRY(c, hipEventCreate(&e0));
@@ -1228,7 +1231,7 @@ int vgr_autotune(vgr_ctx *c, const vgr_settings *st, int64_t n, const float *mea
     c->timing = false;
     float best = 1e30f;
     int bi = -1, rc = VGR_OK;
-    for (int k = 0; k < VGR_TUNE_CANDIDATES && !rc; ++k) {
+    for (int k = 0; k < distinct && !rc; ++k) {
         vgr_settings s2 = *st;
         s2.tile_w = cand[k][0];
         s2.tile_h = cand[k][1];
@@ -1245,7 +1248,8 @@ int vgr_autotune(vgr_ctx *c, const vgr_settings *st, int64_t n, const float *mea
         (void)hipEventSynchronize(e1);
         (void)hipEventElapsedTime(&ms, e0, e1);
         ms /= iters;
-        if (ms_per_candidate) ms_per_candidate[k] = ms;
+        for (int q = k; ms_per_candidate && q < VGR_TUNE_CANDIDATES; q += distinct)
+            ms_per_candidate[q] = ms;
         if (ms < best) { best = ms; bi = k; }
     }
     c->timing = timing;
