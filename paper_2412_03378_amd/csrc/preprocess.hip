@@ -1325,7 +1325,9 @@ __global__ __launch_bounds__(128) void preprocess_bwd_kernel(
     // neighbours'; scattered partial-line stores without a prior read of the
     // lines are slow), and are summed there over the views: 154 registers
     // instead of 200, a third more waves (16 views of 3M Gaussians: 1200 -> 1020 us,
-    // one of 1M: 101 -> 97).
+    // one of 1M: 101 -> 97, but 8 views of 500k 145 -> 157).  The stride is even at
+    // degrees 0 and 2, where rows start at 16 bytes and go by wide LDS accesses: an odd
+    // one, free of bank conflicts, takes 8 views of 500k at degree 2 from 101 to 108 us.
     __shared__ float s_sh[128 * LS];
     const int64_t blk0 = (int64_t)blockIdx.x * 128;
     const int64_t i = blk0 + threadIdx.x;
