@@ -3,6 +3,8 @@
 // include it.
 #pragma once
 
+#include <type_traits>
+
 #include "raster_common.h"
 
 namespace vgr {
@@ -348,7 +350,9 @@ __device__ __forceinline__ void walk_tile_fwd(const RenderParams &rp, const Buff
                 uint64_t mine = 0, over = 0;   // entries the pixel blends; clamped ones (BLOCKS)
                 // lanes with a record left (the loop and its masks are wave-uniform)
                 uint64_t left = __builtin_amdgcn_ballot_w64(mk != 0) & alive[k];
-                if (left != 0) do {
+                // ODD: some colour of the list so far is not finite
+                auto blend = [&](auto ODD) {
+                do {
                     const bool has = __builtin_amdgcn_inverse_ballot_w64(left);
                     const int qi = lowest_bit(mk);   // 31 if none
                     const uint32_t entry = CULL ? st.item[qi] : (uint32_t)qi;
@@ -394,9 +398,7 @@ __device__ __forceinline__ void walk_tile_fwd(const RenderParams &rp, const Buff
                     const bool dob = __builtin_amdgcn_inverse_ballot_w64(dom);
                     const float wgt = dob ? wa * T[k] : 0.0f;
                     float c0 = fr.c0, c1 = fr.c1, c2 = fr.c2;
-                    if (__builtin_expect(anyodd, 0)) {
-                        // (the empty asm keeps this a branch)
-                        asm volatile("" : "+v"(c0), "+v"(c1), "+v"(c2));
+                    if constexpr (ODD) {
                         c0 = dob ? c0 : 0.0f;
                         c1 = dob ? c1 : 0.0f;
                         c2 = dob ? c2 : 0.0f;
@@ -421,6 +423,11 @@ __device__ __forceinline__ void walk_tile_fwd(const RenderParams &rp, const Buff
                     if (COUNT) n.blend += dob ? 1u : 0u;
                     left = __builtin_amdgcn_ballot_w64(mk != 0) & alive[k];
                 } while (left != 0);
+                };
+                if (left != 0) {
+                    if (anyodd) blend(std::true_type{});
+                    else blend(std::false_type{});
+                }
                 if constexpr (BLOCKS) {
                     const bool anyclamp = wave_any(over != 0);
                     b.qmask[bq * 16 + word] = mine;
