@@ -425,6 +425,12 @@ __device__ __forceinline__ void block_fwd(const RenderParams &rp, const Buffers 
         b.wg_time[wg] = make_uint2(cu_key(), (uint32_t)(wg_clock() - t_start));
 }
 
+// Workgroups g = 0 .. color_workgroups() - 1 lie in rows of 2^kGridRow: a grid
+// dimension has fewer than 2^32 threads, and so fewer than 2^26 of these workgroups,
+// the regions of 16 views of 16384x16384.
+constexpr int kGridRow = 20;
+__device__ __forceinline__ uint32_t workgroup() { return (blockIdx.y << kGridRow) + blockIdx.x; }
+
 // First the long tiles, one wave per block, then the others, one wave per region
 // (CULL: tiles are larger than a region).
 template <bool CULL, int MODE, bool COUNT>
@@ -437,18 +443,18 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(6))) void co
     const int lnr = log2_regions(rp);
     const uint32_t nlong = b.d_total[3];
     const uint32_t wlong = ((nlong + 7u) / 8u * 8u) << (lnr + 2);   // their workgroups
+    const uint32_t g = workgroup();
     uint32_t slot;
-    if (blockIdx.x < wlong) {
-        const int q = part_of(blockIdx.x, lnr + 2, slot);
+    if (g < wlong) {
+        const int q = part_of(g, lnr + 2, slot);
         if (slot < nlong)
-            block_fwd<MODE, COUNT>(rp, b, *reinterpret_cast<Block *>(lds), (int)b.tile_order[slot], q,
-                                   blockIdx.x);
+            block_fwd<MODE, COUNT>(rp, b, *reinterpret_cast<Block *>(lds), (int)b.tile_order[slot], q, g);
     } else {
-        const int rgn = part_of(blockIdx.x - wlong, lnr, slot);
+        const int rgn = part_of(g - wlong, lnr, slot);
         slot += nlong;
         if (slot < (uint32_t)rp.total_tiles)
             walk_tile_fwd<8, 8, MODE, COUNT, 64, CULL>(rp, b, *reinterpret_cast<Walk *>(lds),
-                                                       (int)b.tile_order[slot], rgn, blockIdx.x);
+                                                       (int)b.tile_order[slot], rgn, g);
     }
 }
 
@@ -885,18 +891,19 @@ __global__ __launch_bounds__(64) void color_bwd_kernel(RenderParams rp, Buffers 
     const int lnr = log2_regions(rp);
     const uint32_t nlong = b.d_total[3];
     const uint32_t wlong = ((nlong + 7u) / 8u * 8u) << (lnr + 2);   // their workgroups
+    const uint32_t g = workgroup();
     uint32_t slot;
-    if (blockIdx.x < wlong) {
-        const int q = part_of(blockIdx.x, lnr + 2, slot);
+    if (g < wlong) {
+        const int q = part_of(g, lnr + 2, slot);
         if (slot < nlong)
             blocks_bwd<MODE, COUNT, 1>(rp, b, *reinterpret_cast<One *>(lds), (int)b.tile_order[slot],
-                                       q, wg_half + blockIdx.x);
+                                       q, wg_half + g);
     } else {
-        const int rgn = part_of(blockIdx.x - wlong, lnr, slot);
+        const int rgn = part_of(g - wlong, lnr, slot);
         slot += nlong;
         if (slot < (uint32_t)rp.total_tiles)
             blocks_bwd<MODE, COUNT, 4>(rp, b, *reinterpret_cast<Four *>(lds),
-                                       (int)b.tile_order[slot], rgn * 4, wg_half + blockIdx.x);
+                                       (int)b.tile_order[slot], rgn * 4, wg_half + g);
     }
 }
 
@@ -910,9 +917,15 @@ int64_t color_workgroups(const RenderParams &rp)
     return cap * blocks + ((int64_t)rp.total_tiles + 7) / 8 * 8 * (blocks / 4);
 }
 
+static dim3 color_grid(const RenderParams &rp)
+{
+    const int64_t n = color_workgroups(rp), row = (int64_t)1 << kGridRow;
+    return n <= row ? dim3((unsigned)n) : dim3((unsigned)row, (unsigned)((n + row - 1) / row));
+}
+
 hipError_t launch_color_fwd(const RenderParams &rp, const Buffers &b, bool count, hipStream_t s)
 {
-    const dim3 grid((unsigned)color_workgroups(rp));
+    const dim3 grid = color_grid(rp);
     const bool cull = rp.tile_w * rp.tile_h > 64;
 #define VGR_FWD(M)                                                                        \
     do {                                                                                  \
@@ -931,7 +944,7 @@ hipError_t launch_color_fwd(const RenderParams &rp, const Buffers &b, bool count
 hipError_t launch_color_bwd(const RenderParams &rp, const Buffers &b, bool count, hipStream_t s)
 {
     const int64_t wg_half = color_workgroups(rp);
-    const dim3 grid((unsigned)wg_half);
+    const dim3 grid = color_grid(rp);
 #define VGR_BWD(M)                                                                  \
     do {                                                                            \
         if (count) color_bwd_kernel<M, true><<<grid, 64, 0, s>>>(rp, b, wg_half);   \
