@@ -1125,6 +1125,9 @@ __device__ inline uint32_t bucket_min(int k)
 // d_total[3]: the long tiles, which the colour rasterisers give to one wave per 4x4
 // block: those of the buckets whose lists reach 1 / kLongShare of all instances, at
 // most long_max of them; every tile of a frame that has room for all (long_tiles_max).
+// Over 2048 regions, whose waves fill the chip, a list of less than kLongMin entries is
+// never long (a frame that has room for all: unless its lists are longer on average than
+// kLongMean).
 //
 // A region walked by one wave takes about 0.1 us per entry, all regions together
 // about 50 ps per instance, so one list of 1/2000 of the instances takes as long as
@@ -1133,11 +1136,18 @@ __device__ inline uint32_t bucket_min(int k)
 // 1/4096 and 1/8192 (1/2048 and 1/1024 were slower throughout): 1280x720 with 300k
 // Gaussians 78/120 and 66/105, 600k 118/181 and 133/189, 1.2M 185/273 and 186/289,
 // 2.4M 271/433 and 293/456; 1920x1080 with 1M 253/435 and 256/439.
-constexpr uint32_t kLongShare = 4096;
+// Lists of less than a batch win little by a wave per block and cost three waves more.
+// Forward / backward us without kLongMin and with it: 640x480 with 30k small Gaussians
+// 17/29 and 12/25, 20k of mixed sizes 23/42 and 21/37; 576x400 (3600 regions) with
+// 100k small ones, 40 entries a region, 23/34 and 18/34; but 400k of mixed sizes, 560 a
+// region, 90/152 and (at 96) 95/165, and at 240x180 (690 regions) 5k of mixed sizes
+// 10/14 and 11/21.
+constexpr uint32_t kLongShare = 4096, kLongMin = 48, kLongMean = 64;
 
 __global__ void tile_place_kernel(const uint2 *__restrict__ ranges, const uint32_t *__restrict__ hist,
                                   uint32_t *__restrict__ cursor, uint32_t *__restrict__ order,
-                                  int32_t n, uint32_t *__restrict__ d_total, uint32_t long_max)
+                                  int32_t n, uint32_t *__restrict__ d_total, uint32_t long_max,
+                                  uint32_t regions)
 {
     __shared__ uint32_t base[32], local[32], start[32];
     if (threadIdx.x < 32) local[threadIdx.x] = 0;
@@ -1145,10 +1155,13 @@ __global__ void tile_place_kernel(const uint2 *__restrict__ ranges, const uint32
         uint32_t acc = 0, nlong = 0;
         const uint32_t K = d_total[0];
         const bool all_long = long_max >= (uint32_t)n;   // a small frame
+        const bool full = regions > 2048u;
+        uint32_t least = all_long ? 0u : K / kLongShare;
+        if (full && !(all_long && K / kLongMean >= regions)) least = max(least, kLongMin);
         for (int k = 0; k < 32; ++k) {
             base[k] = acc;
             acc += hist[k];
-            if (k < 31 && (all_long || bucket_min(k) >= K / kLongShare)) nlong = acc;
+            if (k < 31 && bucket_min(k) >= least) nlong = acc;
         }
         if (blockIdx.x == 0) d_total[3] = min(nlong, long_max);
     }
@@ -1728,7 +1741,8 @@ hipError_t launch_tile_order(const RenderParams &rp, const Buffers &b, bool clea
     tile_hist_kernel<<<grid_for(total_tiles, 256), 256, 0, s>>>(b.ranges, hist, total_tiles);
     tile_place_kernel<<<grid_for(total_tiles, 256), 256, 0, s>>>(b.ranges, hist, cursor,
                                                                   b.tile_order, total_tiles, b.d_total,
-                                                                  (uint32_t)long_tiles_max(total_tiles, rp.tile_w, rp.tile_h));
+                                                                  (uint32_t)long_tiles_max(total_tiles, rp.tile_w, rp.tile_h),
+                                                                  (uint32_t)((int64_t)total_tiles * (rp.tile_w * rp.tile_h / 64)));
     return hipGetLastError();
 }
 

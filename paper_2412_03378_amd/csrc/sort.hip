@@ -7,9 +7,9 @@
 // Radix pass = histogram kernel + per-digit exclusive scan of the digit-major
 // table of per-block counts (one block per digit) + scatter kernel, which adds
 // the digit starts (a scan of the 256 digit totals) itself.  The scatter ranks
-// keys stably inside a 4096-key tile: each wave owns 1024 consecutive keys,
-// ranks 64 keys at a time by matching digits with one ballot per digit bit,
-// and keeps running per-digit counters in LDS.  The tile is then reordered by
+// keys stably inside a tile of 1024, 2048 or 4096 keys (keys_per_thread): each wave owns
+// a quarter of them, consecutive, ranks 64 keys at a time by matching digits with one
+// ballot per digit bit, and keeps running per-digit counters in LDS.  The tile is then reordered by
 // digit in LDS and written out run by run, so that neighbouring threads write
 // neighbouring addresses.  Up to kOneMax pairs are sorted by one workgroup in one
 // launch.

@@ -226,13 +226,14 @@ __host__ __device__ inline size_t quad_batch(uint32_t start, int t)
 constexpr uint32_t kFlagClamp = 1u, kFlagOdd = 2u;
 // Most tiles the colour rasterisers treat as long (one wave per 4x4 block, the first
 // d_total[3] of tile_order): 2048 regions of 8x8 pixels, whose 8192 waves fill the
-// chip once, or every tile of a frame of at most 8192 regions (640x480 with 8x8 tiles:
-// 93 / 92 us as blocks, 271 / 263 as regions; 1280x720 with 600k Gaussians, 14400
-// regions: slower as blocks).
+// chip once, or every tile of a frame of at most 4096 regions.  Forward + backward us
+// of 30k and 300k small Gaussians and 400k of mixed sizes, every tile as blocks and only
+// the long ones: 480x360 (2700 regions) 40, 94, 198 and 42, 120, 291; 640x480 (4800) 56,
+// 118, 294 and 45, 111, 342; 960x540 (8160) 80, 153, 452 and 46, 126, 381.
 inline __host__ __device__ int32_t long_tiles_max(int32_t total_tiles, int tile_w, int tile_h)
 {
     const int32_t regions = tile_w * tile_h / 64;
-    const int32_t cap = (int64_t)total_tiles * regions <= 8192 ? total_tiles : 2048 / regions;
+    const int32_t cap = (int64_t)total_tiles * regions <= 4096 ? total_tiles : 2048 / regions;
     return cap < total_tiles ? cap : total_tiles;
 }
 inline int64_t quad_batches(int64_t instances, int32_t total_tiles)
