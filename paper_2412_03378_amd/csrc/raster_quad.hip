@@ -608,7 +608,10 @@ __device__ __forceinline__ void blocks_bwd(const RenderParams &rp, const Buffers
         if constexpr (BPW == 4) {
             st.pix[lane] = make_float4(un, g0, g1, g2);
             st.run[lane] = make_float2(T, GB);
-            for (int i = lane; i < 65 * kAcc; i += 64) st.acc[i] = 0.0f;
+            // the sums of the entries that a batch has, to the end of their last four,
+            // which leave together below (the pad's are never read)
+            const int sums = ((int)min(range.y - range.x, 64u) + 3) / 4 * 4 * kAcc;
+            for (int i = lane; i < sums; i += 64) st.acc[i] = 0.0f;
         }
         // record 64, named by the slots past a block's survivors, is read with no
         // lane blending: it has to hold finite values
