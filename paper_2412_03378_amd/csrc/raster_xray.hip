@@ -44,9 +44,9 @@
 // records and a transpose-reduce per record (before) -> this:
 //   12 x 160x160, 8k Gaussians, 8x8 tiles         53 / 164 ->  50 / 70
 //   8 x 256x256, 60k, 8x8                        355 / 1110 -> 295 / 332
-//   64 x 512x512, 500k, 16x16 (371M instances) 56400 / 123600 -> 37900 / 58500
-// (87 and 133 cycles per visit of 64 pairs; a backward that held pixels in its lanes took
-// 68800.)
+//   64 x 512x512, 500k, 16x16 (371M instances) 56400 / 123600 -> 37700 / 59100
+// (87 and 134 cycles per visit of 64 pairs; a backward that held pixels in its lanes took
+// 68800, and one that decides by the ray frame also next to the cut 58500.)
 #include "raster_common.h"
 
 namespace vgr {
